@@ -4,9 +4,9 @@
 //   out = sum_j exp(s_j) v_j / sum_j exp(s_j),
 //   s_j = scale q.C_k[j] + beta[j]  (j < t),   s_j = scale q.K[j - t]  (suffix).
 // Decode-shaped (a few query rows per KV head): one wave per (KV head, key
-// split), 64-key chunks with 16-byte loads; lane = key for the logits,
-// lane = feature for P.V with the V rows staged in LDS; online softmax over
-// the chunks; splits merged by a second kernel.  fp32 arithmetic.
+// split), register-resident; more rows: the fp32 matrix instructions.  Online
+// softmax over the chunks of a split; splits merged by a second kernel.  fp32
+// arithmetic.
 #pragma once
 #include "common.hpp"
 #include "misc.hpp"
@@ -14,8 +14,16 @@
 namespace still {
 
 constexpr int ATTEND_MAX_ROWS = 32;   // group * n_queries
-constexpr int ATTEND_DECODE_ROWS = 8; // at most this many rows: the register-resident decode kernel
-constexpr int ATTEND_KC = 64;         // keys per chunk: one per lane for the logits
+// Rows per KV head up to which the register-resident decode kernel is taken
+// instead of the matrix one (bf16, us per call, decode / matrix).  8 heads, 2
+// rows: 1088 keys of width 256 11.2 / 16.0, 65600 keys 110 / 118.  4 rows over
+// few keys in all: 8 heads x 1088 keys of width 128 7.8 / 9.5 in the kernel,
+// of width 256 13.2 / 15.8; over many: 8 x 131136 of width 128 152 / 114, 64 x
+// 719 19.6 / 14.1, 8 x 65536 of width 256 160 / 114.  8 rows: 8 x 1088 keys
+// 17.5 / 11.8 and (width 256) 30.6 / 16.1.
+inline __host__ __device__ int attend_decode_rows(int d, int heads, long keys) {
+  return d >= 128 && heads * keys <= 12288 ? 4 : 2;
+}
 
 struct ConsumerArgs {
   const void* q;        // [H*group][nq][D]
@@ -41,29 +49,6 @@ __device__ __forceinline__ void rope_angle(double pos, int jh, int d, double the
   double phi = pos * inv;
   phi -= 6.283185307179586 * rint(phi * 0.15915494309189535);
   sincosf((float)phi, &s, &c);
-}
-
-// Per-(element type, head width) tiling of one chunk.  A key row is PPR
-// 16-byte pieces; the V rows of a chunk are staged through LDS VROWS at a
-// time so that a lane holds at most 16 pieces in flight; K rows are read
-// lane = key, KSLAB pieces per round trip.
-template <class IT, int D>
-struct AttendTile {
-  static constexpr int ROWB = D * (int)sizeof(IT);
-  static constexpr int PPR = ROWB / 16;
-  static constexpr int EPP = 16 / (int)sizeof(IT);        // elements per piece
-  static constexpr int VROWS = 16384 / ROWB < ATTEND_KC ? 16384 / ROWB : ATTEND_KC;
-  static constexpr int VPL = VROWS * PPR / 64;             // V pieces per lane per pass
-  static constexpr int KSLAB = PPR < 16 ? PPR : 16;
-  static constexpr int FPL = D / 64;                       // output features per lane
-  static_assert(VROWS * PPR % 64 == 0 && PPR % KSLAB == 0, "tile shape");
-};
-
-// dynamic LDS: q rows fp32 [RB][D] (rows past R zero) | V pass [VROWS][ROWB] | P [64][RB]
-template <class IT, int D>
-inline size_t attend_lds_bytes(int RB) {
-  using TL = AttendTile<IT, D>;
-  return (size_t)RB * D * 4 + (size_t)TL::VROWS * TL::ROWB + (size_t)ATTEND_KC * RB * 4;
 }
 
 // 16-byte pieces as a native vector: plain loads and stores (a HIP uint4 copy
@@ -96,178 +81,297 @@ struct AttendChunk {
   bool compact;
 };
 
-template <class IT, int D>
+template <class IT, int D, int KC>
 __device__ __forceinline__ AttendChunk attend_chunk(const ConsumerArgs& a, int h, int c) {
   constexpr long ROWB = (long)D * sizeof(IT);
-  const int nck = (a.t + ATTEND_KC - 1) / ATTEND_KC;
+  const int nck = (a.t + KC - 1) / KC;
   AttendChunk k;
   k.compact = c < nck;
   k.rows = k.compact ? a.t : a.S;
-  k.j0 = (k.compact ? c : c - nck) * ATTEND_KC;
+  k.j0 = (k.compact ? c : c - nck) * KC;
   const long hoff = (long)h * k.rows * ROWB;
   k.kbase = (const char*)(k.compact ? a.ck : a.k) + hoff;
   k.vbase = (const char*)(k.compact ? a.cv : a.v) + hoff;
   return k;
 }
 
-template <class IT, int D>
-__device__ __forceinline__ void attend_load_v(const AttendChunk& ch, int vb, int lane,
-                                              u32x4 (&vp)[AttendTile<IT, D>::VPL]) {
-  using TL = AttendTile<IT, D>;
+// ---------------------------------------------------------------------------
+// More query rows (prefill-shaped calls, several heads per KV head): both products on the fp32 matrix
+// instructions (operands and sums in fp32, as given), TR = 16 or 32 query rows
+// (rows past R are zero queries, never stored).  A workgroup is 4 waves; wave w
+// takes chunks c0 + w, c0 + w + 4, ... of the split's chunks of 32 keys.
+//   S^T[key][row]: keys are MFMA rows, query rows columns, so a lane owns one
+//   query row and the softmax statistics stay in the lane.  Lane group lg of
+//   key l reads 16-byte pieces LG i + lg of the key's row: the pairing of
+//   contraction indices is free, so the pieces feed the product as loaded,
+//   against the query row in LDS.
+//   O^T[feature][row]: accumulator register j of S^T holds the keys
+//   row(j, lg), the B operand of one P.V step; lane l reads the D / TR
+//   consecutive features [l D / TR, ..) of that key's V row, one per output
+//   tile, so the V rows are read whole and nothing is exchanged.
+// V of a chunk is loaded ahead of its logits and K of the next one ahead of
+// the softmax (rows up to 512 bytes).  The waves' partials are combined in LDS.
+// A chunk of 32 keys costs 8192 cycles of the matrix pipe at 32 rows and
+// D = 128, 4.6 TB/s of bf16 keys and values over the chip: about what memory
+// delivers.  32 rows over a 655-entry prefix and a 4099-token suffix (8 heads,
+// d = 128): 143 us with FMAs from LDS-resident queries, one wave per split; 21 us.
+// ---------------------------------------------------------------------------
+constexpr int ATTEND_WAVES = 4;
+
+template <int TR> struct AttendMma;
+template <> struct AttendMma<32> {
+  typedef f32x16 acc;
+  static __device__ __forceinline__ void mma(acc& c, float a, float b) {
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+  }
+};
+template <> struct AttendMma<16> {
+  typedef f32x4 acc;
+  static __device__ __forceinline__ void mma(acc& c, float a, float b) {
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+};
+
+// B bytes at p (B-byte aligned, B = 4, 8 or a multiple of 16) into words
+template <int B> __device__ __forceinline__ void load_words(const char* p, uint32_t (&w)[B / 4]) {
+  if constexpr (B == 4) {
+    w[0] = *(const uint32_t*)p;
+  } else if constexpr (B == 8) {
+    const uint2 u = *(const uint2*)p;
+    w[0] = u.x;
+    w[1] = u.y;
+  } else {
 #pragma unroll
-  for (int i = 0; i < TL::VPL; ++i) {
-    const int pc = lane + 64 * i, row = pc / TL::PPR, col = pc % TL::PPR;
-    vp[i] = ((const u32x4*)(ch.vbase + (long)min(ch.j0 + vb + row, ch.rows - 1) * TL::ROWB))[col];
+    for (int i = 0; i < B / 16; ++i) {
+      const u32x4 u = ((const u32x4*)p)[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[4 * i + e] = u[e];
+    }
   }
 }
+template <class IT> __device__ __forceinline__ float word_elem(const uint32_t* w, int e) {
+  if constexpr (sizeof(IT) == 4) return __uint_as_float(w[e]);
+  else return __uint_as_float(e & 1 ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16);
+}
 
-// Query rows R > 8 (prefill-shaped calls): lane = key for the logits with the
-// query rows read from LDS, lane = features for P.V with V staged in LDS and
-// the probabilities exchanged through LDS.  RB: bound on R (register arrays).
-template <class IT, int D, int RB>
-__global__ __launch_bounds__(64) void attend_partial_kernel(ConsumerArgs a) {
-  using TL = AttendTile<IT, D>;
-  constexpr int FPL = TL::FPL;
+// dynamic LDS: q rows fp32 [TR][D + 4], later the combined output rows | per-wave key bias [4][KC] | m, l [4][TR]
+template <int D, int TR>
+inline size_t attend_lds_bytes() {
+  return sizeof(float) * ((size_t)TR * (D + 4) + ATTEND_WAVES * ATTEND_KC + 2 * ATTEND_WAVES * TR);
+}
+
+template <class IT, int D, int TR>
+__global__ __launch_bounds__(64 * ATTEND_WAVES) void attend_rows_kernel(ConsumerArgs a) {
+  typedef AttendMma<TR> MM;
+  constexpr int KC = ATTEND_KC, LG = 64 / TR, CR = TR * TR / 64, NKT = KC / TR;
+  constexpr int ROWB = D * (int)sizeof(IT), EPP = 16 / (int)sizeof(IT), NP = ROWB / 16 / LG;
+  constexpr int FPT = D / TR, VB = FPT * (int)sizeof(IT), LQ = D + 4;
+  constexpr bool AHEAD = ROWB <= 512;
+  static_assert(NP >= 1 && NKT >= 1 && CR % 4 == 0, "tile shape");
   extern __shared__ float4 attend_smem[];
-  const int R = a.group * a.nq;
-  float* qs = (float*)attend_smem;                                   // [RB][D]
-  char* vs = (char*)(qs + RB * D);                                    // [VROWS][ROWB]
-  float* ps = (float*)(vs + TL::VROWS * TL::ROWB);                    // [64][RB]
-  const int lane = threadIdx.x;
-  const int split = blockIdx.x, h = blockIdx.y;
-  const int nchunks = (a.t + ATTEND_KC - 1) / ATTEND_KC + (a.S + ATTEND_KC - 1) / ATTEND_KC;
+  float* qs = (float*)attend_smem;                     // [TR][LQ]
+  float* kbias = qs + TR * LQ;                         // [waves][KC]: bias of a chunk's keys
+  float* wm = kbias + ATTEND_WAVES * KC;               // [waves][TR]
+  float* wl = wm + ATTEND_WAVES * TR;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l = lane % TR, lg = lane / TR;
+  const int split = blockIdx.x, h = blockIdx.y, R = a.group * a.nq;
+  const int nchunks = (a.t + KC - 1) / KC + (a.S + KC - 1) / KC;
   const int c0 = split * a.cps, c1 = min(nchunks, c0 + a.cps);   // this split's chunks [c0, c1)
-  {  // query rows g*nq + i of KV head h are contiguous: 16-byte pieces, fp32 in LDS
+  {  // query rows g*nq + i of KV head h are contiguous: 16-byte pieces, fp32 in LDS, rows past R zero
     const u32x4* qh = (const u32x4*)((const IT*)a.q + (long)h * R * D);
-    const int np = R * D / TL::EPP;
-#pragma unroll 4
-    for (int pc = lane; pc < np; pc += 64) {
-      float f[TL::EPP];
-      unpack16<IT>(qh[pc], f);
+    for (int pc = tid; pc < TR * (D / EPP); pc += 64 * ATTEND_WAVES) {
+      const int r = pc / (D / EPP), x = (pc - r * (D / EPP)) * EPP;
+      float f[EPP];
 #pragma unroll
-      for (int e = 0; e < TL::EPP; e += 4)
-        *(float4*)&qs[pc * TL::EPP + e] = make_float4(f[e], f[e + 1], f[e + 2], f[e + 3]);
+      for (int e = 0; e < EPP; ++e) f[e] = 0.f;
+      if (r < R) unpack16<IT>(qh[pc], f);
+#pragma unroll
+      for (int e = 0; e < EPP; e += 4) *(float4*)&qs[r * LQ + x + e] = make_float4(f[e], f[e + 1], f[e + 2], f[e + 3]);
     }
   }
   __syncthreads();
-  if (a.qpos) {  // RoPE of the query rows at their logical positions (rotate-half pairs)
+  if (a.qpos) {  // RoPE of the query rows at their logical positions (rotate-half pairs): one angle for the group's heads
     constexpr int HD = D / 2;
-    for (int e = lane; e < R * HD; e += 64) {
-      const int r = e / HD, j = e % HD;
+    for (int e = tid; e < a.nq * HD; e += 64 * ATTEND_WAVES) {
+      const int i = e / HD, j = e % HD;
       float c, sn;
-      rope_angle(a.qpos[r % a.nq], j, D, a.theta, c, sn);
-      const float x0 = qs[r * D + j], x1 = qs[r * D + j + HD];
-      qs[r * D + j] = x0 * c - x1 * sn;
-      qs[r * D + j + HD] = x1 * c + x0 * sn;
+      rope_angle(a.qpos[i], j, D, a.theta, c, sn);
+      for (int r = i; r < R; r += a.nq) {
+        const float x0 = qs[r * LQ + j], x1 = qs[r * LQ + j + HD];
+        qs[r * LQ + j] = x0 * c - x1 * sn;
+        qs[r * LQ + j + HD] = x1 * c + x0 * sn;
+      }
     }
     __syncthreads();
   }
 
-  float m[RB], l[RB], o[RB][FPL];
+  typename MM::acc o[FPT];
 #pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    m[r] = -INFINITY;
-    l[r] = 0.f;
+  for (int f = 0; f < FPT; ++f)
 #pragma unroll
-    for (int u = 0; u < FPL; ++u) o[r][u] = 0.f;
+    for (int j = 0; j < CR; ++j) o[f][j] = 0.f;
+  float m = -INFINITY, ls = 0.f;
+  const int lim = a.causal ? a.S - a.nq + l % a.nq : 0x7fffffff;   // row g*nq+i sees suffix rows <= S-nq+i
+  auto key_of = [&](int kt, int j) { return kt * TR + 4 * LG * (j >> 2) + 4 * lg + (j & 3); };   // within the chunk
+
+  u32x4 kp[NKT][NP];
+  auto load_k = [&](const AttendChunk& ch) {
+#pragma unroll
+    for (int kt = 0; kt < NKT; ++kt) {
+      const u32x4* kr = (const u32x4*)(ch.kbase + (long)min(ch.j0 + kt * TR + l, ch.rows - 1) * ROWB);
+#pragma unroll
+      for (int i = 0; i < NP; ++i) kp[kt][i] = kr[LG * i + lg];
+    }
+  };
+  auto load_bias = [&](const AttendChunk& ch) -> float {   // lane = key (KC of them)
+    const int jl = ch.j0 + lane % KC;
+    return jl < ch.rows && ch.compact && a.beta ? a.beta[(long)h * a.t + jl] : 0.f;
+  };
+  float bias = 0.f;
+  if (AHEAD && c0 + w < c1) {
+    const AttendChunk ch = attend_chunk<IT, D, KC>(a, h, c0 + w);
+    load_k(ch);
+    bias = load_bias(ch);
   }
-  for (int c = c0; c < c1; ++c) {
-    const AttendChunk ch = attend_chunk<IT, D>(a, h, c);
-    // ---- logits, lane = key (row jl of the part; rows past its end are clamped and masked)
-    const int jl = ch.j0 + lane;
-    const u32x4* kr = (const u32x4*)(ch.kbase + (long)min(jl, ch.rows - 1) * TL::ROWB);
-    float s[RB];
+  for (int c = c0 + w; c < c1; c += ATTEND_WAVES) {
+    const AttendChunk ch = attend_chunk<IT, D, KC>(a, h, c);
+    uint32_t vr[NKT * CR][VB / 4];
+    auto load_v = [&]() {
 #pragma unroll
-    for (int r = 0; r < RB; ++r) s[r] = 0.f;
+      for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
-    for (int sb = 0; sb < TL::PPR; sb += TL::KSLAB) {
-      u32x4 kp[TL::KSLAB];
+        for (int j = 0; j < CR; ++j)
+          load_words<VB>(ch.vbase + (long)min(ch.j0 + key_of(kt, j), ch.rows - 1) * ROWB + l * VB, vr[kt * CR + j]);
+    };
+    if constexpr (AHEAD) {
+      load_v();
+    } else {
+      load_k(ch);
+      bias = load_bias(ch);
+    }
+    // ---- logits
+    typename MM::acc s[NKT];
 #pragma unroll
-      for (int i = 0; i < TL::KSLAB; ++i) kp[i] = kr[sb + i];
+    for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
-      for (int i = 0; i < TL::KSLAB; ++i) {
-        float kv[TL::EPP];
-        unpack16<IT>(kp[i], kv);
-        const int f0 = (sb + i) * TL::EPP;
+      for (int j = 0; j < CR; ++j) s[kt][j] = 0.f;
 #pragma unroll
-        for (int r = 0; r < RB; ++r) {
-          if (r < R) {
+    for (int i = 0; i < NP; ++i) {
+      float qv[EPP];
 #pragma unroll
-            for (int e = 0; e < TL::EPP; e += 4) {
-              const float4 qv = *(const float4*)&qs[r * D + f0 + e];
-              s[r] += qv.x * kv[e] + qv.y * kv[e + 1] + qv.z * kv[e + 2] + qv.w * kv[e + 3];
-            }
-          }
-        }
+      for (int e = 0; e < EPP; e += 4) {
+        const float4 u = *(const float4*)&qs[l * LQ + (LG * i + lg) * EPP + e];
+        qv[e] = u.x;
+        qv[e + 1] = u.y;
+        qv[e + 2] = u.z;
+        qv[e + 3] = u.w;
+      }
+#pragma unroll
+      for (int kt = 0; kt < NKT; ++kt) {
+        float kv[EPP];
+        unpack16<IT>(kp[kt][i], kv);
+#pragma unroll
+        for (int e = 0; e < EPP; ++e) MM::mma(s[kt], kv[e], qv[e]);
       }
     }
-    const bool valid = jl < ch.rows;
-    const float bj = (ch.compact && valid && a.beta) ? a.beta[(long)h * a.t + jl] : 0.f;
-    // ---- online softmax per row over the chunk; P to LDS
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      if (r >= R) continue;
-      const bool ok = valid && (ch.compact || !a.causal || jl <= a.S - a.nq + r % a.nq);   // row g*nq+i
-      const float sv = ok ? s[r] * a.scale + bj : -INFINITY;
-      float cm = sv;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) cm = fmaxf(cm, __shfl_xor(cm, off));
-      const float mn = fmaxf(m[r], cm);
-      const float mref = mn == -INFINITY ? 0.f : mn;
-      const float p = expf(sv - mref);
-      float cs = p;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) cs += __shfl_xor(cs, off);
-      const float al = expf(m[r] - mref);
-      l[r] = l[r] * al + cs;
-#pragma unroll
-      for (int u = 0; u < FPL; ++u) o[r][u] *= al;
-      m[r] = mn;
-      ps[lane * RB + r] = p;
+    if (lane < KC) kbias[w * KC + lane] = bias;   // (this wave's slot; read back below in program order)
+    if constexpr (AHEAD) {
+      if (c + ATTEND_WAVES < c1) {
+        const AttendChunk nx = attend_chunk<IT, D, KC>(a, h, c + ATTEND_WAVES);
+        load_k(nx);
+        bias = load_bias(nx);
+      }
+    } else {
+      load_v();
     }
-    // ---- P.V through LDS, VROWS rows per pass; lane = features [lane*FPL, (lane+1)*FPL)
+    __builtin_amdgcn_wave_barrier();
+    // ---- online softmax: this lane's row, its keys of the chunk
+    float cm = -INFINITY;
 #pragma unroll
-    for (int vb = 0; vb < ATTEND_KC; vb += TL::VROWS) {
-      u32x4 vp[TL::VPL];
-      attend_load_v<IT, D>(ch, vb, lane, vp);
-      __syncthreads();   // previous readers of vs are done; ps is complete
+    for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
-      for (int i = 0; i < TL::VPL; ++i) ((u32x4*)vs)[lane + 64 * i] = vp[i];
-      __syncthreads();
-#pragma unroll 4
-      for (int kk = 0; kk < TL::VROWS; ++kk) {
-        float vv[FPL];
-        const IT* vrow = (const IT*)(vs + kk * TL::ROWB) + lane * FPL;
+      for (int jq = 0; jq < CR / 4; ++jq) {
+        const float4 b = *(const float4*)&kbias[w * KC + key_of(kt, 4 * jq)];
+        const float bv[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
-        for (int u = 0; u < FPL; ++u) vv[u] = to_f32(vrow[u]);
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-          if (r >= R) continue;
-          const float p = ps[(vb + kk) * RB + r];
-#pragma unroll
-          for (int u = 0; u < FPL; ++u) o[r][u] += p * vv[u];
+        for (int u = 0; u < 4; ++u) {
+          const int jl = ch.j0 + key_of(kt, 4 * jq) + u;
+          const bool ok = jl < ch.rows && (ch.compact || jl <= lim);
+          s[kt][4 * jq + u] = ok ? s[kt][4 * jq + u] * a.scale + bv[u] : -INFINITY;
+          cm = fmaxf(cm, s[kt][4 * jq + u]);
         }
       }
+#pragma unroll
+    for (int off = TR; off < 64; off <<= 1) cm = fmaxf(cm, __shfl_xor(cm, off));
+    const float mn = fmaxf(m, cm);
+    const float mref = mn == -INFINITY ? 0.f : mn;
+    float cs = 0.f;
+#pragma unroll
+    for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+      for (int j = 0; j < CR; ++j) {
+        s[kt][j] = expf(s[kt][j] - mref);
+        cs += s[kt][j];
+      }
+#pragma unroll
+    for (int off = TR; off < 64; off <<= 1) cs += __shfl_xor(cs, off);
+    const float al = expf(m - mref);
+    ls = ls * al + cs;
+    m = mn;
+    if (__any(al != 1.f)) {
+#pragma unroll
+      for (int f = 0; f < FPT; ++f)
+#pragma unroll
+        for (int j = 0; j < CR; ++j) o[f][j] *= al;
     }
-    __syncthreads();   // ps and vs are rewritten by the next chunk
+    // ---- P.V
+#pragma unroll
+    for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+      for (int j = 0; j < CR; ++j)
+#pragma unroll
+        for (int f = 0; f < FPT; ++f) MM::mma(o[f], word_elem<IT>(vr[kt * CR + j], f), s[kt][j]);
   }
-  // ---- split partials
+  // ---- combine the waves (each lane holds its row's m, l and features l' FPT + f,
+  // l' = row(j, lg) of the accumulator) and write the split's partial rows
+  if (lane < TR) {
+    wm[w * TR + l] = m;
+    wl[w * TR + l] = ls;
+  }
+  __syncthreads();   // (also: every wave has read the query rows)
+  float M = wm[l];
+#pragma unroll
+  for (int i = 1; i < ATTEND_WAVES; ++i) M = fmaxf(M, wm[i * TR + l]);
+  const float Mref = M == -INFINITY ? 0.f : M;
+  const float sc = expf(m - Mref);
+  for (int i = 0; i < ATTEND_WAVES; ++i) {
+    if (w == i) {
+#pragma unroll
+      for (int j = 0; j < CR; ++j) {
+        float* dst = &qs[l * LQ + (4 * LG * (j >> 2) + 4 * lg + (j & 3)) * FPT];
+#pragma unroll
+        for (int f = 0; f < FPT; ++f) dst[f] = i == 0 ? o[f][j] * sc : dst[f] + o[f][j] * sc;
+      }
+    }
+    __syncthreads();
+  }
   const long base = ((long)split * a.H + h) * R;
+  for (int e = tid; e < R * (D / 4); e += 64 * ATTEND_WAVES) {
+    const int r = e / (D / 4), x = (e - r * (D / 4)) * 4;
+    *(float4*)(a.opart + (base + r) * D + x) = *(const float4*)&qs[r * LQ + x];
+  }
+  if (tid < R) {   // (tid < TR: lane tid of wave 0 owns row tid, so M and Mref are that row's)
+    float L = 0.f;
 #pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    if (r >= R) continue;
-    float* op = a.opart + (base + r) * D + lane * FPL;
-#pragma unroll
-    for (int u = 0; u < FPL; ++u) op[u] = o[r][u];
-    if (lane == 0) {
-      a.mpart[base + r] = m[r];
-      a.lpart[base + r] = l[r];
-    }
+    for (int i = 0; i < ATTEND_WAVES; ++i) L += expf(wm[i * TR + tid] - Mref) * wl[i * TR + tid];
+    a.mpart[base + tid] = M;
+    a.lpart[base + tid] = L;
   }
 }
 
 // ---------------------------------------------------------------------------
-// Decode-shaped attention (R <= 8 query rows per KV head), no LDS in the chunk
+// Decode-shaped attention (R <= 4 query rows per KV head), no LDS in the chunk
 // loop.  A key row is PPR 16-byte pieces; LPK = PPR lanes share one key (lane
 // piece pl = lane % LPK holds features [pl*EPP, (pl+1)*EPP)), KPI = 64 / LPK
 // keys are read per instruction, NIT instructions make a chunk of KC keys.
@@ -283,7 +387,7 @@ struct DecodeTile {
   static constexpr int LPK = PPR;
   static constexpr int KPI = 64 / LPK;
   static constexpr int EPP = 16 / (int)sizeof(IT);
-  static constexpr int NIT = RB <= 4 ? 8 : 4;
+  static constexpr int NIT = 8;
   static constexpr int KC = NIT * KPI;
   static_assert(LPK >= 8 && LPK <= 64, "lanes per key");
 };

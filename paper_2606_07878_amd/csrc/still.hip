@@ -127,15 +127,19 @@ static still_status attend_plan(const still_attend_config* c, AttendPlan* ap) {
     return fail(STILL_E_SHAPE, "causal attention needs n_suffix >= n_queries");
   if (!std::isfinite(c->scale) || c->scale < 0.f) return fail(STILL_E_INVAL, "scale must be finite and >= 0");
   if (!(c->rope_theta >= 0.0) || !std::isfinite(c->rope_theta)) return fail(STILL_E_INVAL, "rope_theta must be >= 0");
-  // keys per chunk: the decode kernel's KC (rows <= 8) or the LDS kernel's 64
+  // keys per chunk: the decode kernel's KC or ATTEND_KC
   const long R = (long)c->group * c->n_queries;
   const int esize = c->mode == STILL_MODE_FP32 ? 4 : 2;
-  const int kc = R <= ATTEND_DECODE_ROWS ? (R <= 4 ? 8 : 4) * (64 / (c->head_dim * esize / 16)) : ATTEND_KC;
+  const bool decode = R <= attend_decode_rows(c->head_dim, c->n_kv_heads, (long)c->t + c->n_suffix);
+  const int kc = decode ? 8 * (64 / (c->head_dim * esize / 16)) : ATTEND_KC;
   ap->kc = kc;
   const long chunks = ((long)c->t + kc - 1) / kc + ((long)c->n_suffix + kc - 1) / kc;
-  const long per_head = std::max(1L, (long)ATTEND_TARGET_BLOCKS / c->n_kv_heads);
+  // one-wave blocks of the decode kernel; blocks of ATTEND_WAVES waves, a
+  // quarter as many, otherwise (the same number of chunks for every wave)
+  const long unit = decode ? 1 : ATTEND_WAVES;
+  const long per_head = std::max(1L, (long)ATTEND_TARGET_BLOCKS / unit / c->n_kv_heads);
   ap->R = c->group * c->n_queries;
-  ap->cps = (int)((chunks + per_head - 1) / per_head);
+  ap->cps = (int)std::min(rup((chunks + per_head - 1) / per_head, unit), chunks);
   ap->splits = (int)((chunks + ap->cps - 1) / ap->cps);
   const size_t slots = (size_t)ap->splits * c->n_kv_heads * ap->R;
   ap->opart = 0;
@@ -149,17 +153,17 @@ template <class IT, int D>
 static hipError_t launch_attend(const ConsumerArgs& a, hipStream_t st) {
   const int R = a.group * a.nq;
   const dim3 grid(a.splits, a.H);
-  if (R <= 2)
+  const bool decode = R <= attend_decode_rows(D, a.H, (long)a.t + a.S);
+  if (decode && R <= 2)
     hipLaunchKernelGGL((attend_decode_kernel<IT, D, 2>), grid, dim3(64), 0, st, a);
-  else if (R <= 4)
+  else if (decode)
     hipLaunchKernelGGL((attend_decode_kernel<IT, D, 4>), grid, dim3(64), 0, st, a);
-  else if (R <= ATTEND_DECODE_ROWS)
-    hipLaunchKernelGGL((attend_decode_kernel<IT, D, 8>), grid, dim3(64), 0, st, a);
   else if (R <= 16)
-    hipLaunchKernelGGL((attend_partial_kernel<IT, D, 16>), grid, dim3(64), (attend_lds_bytes<IT, D>(16)), st, a);
+    hipLaunchKernelGGL((attend_rows_kernel<IT, D, 16>), grid, dim3(64 * ATTEND_WAVES), (attend_lds_bytes<D, 16>()), st,
+                       a);
   else
-    hipLaunchKernelGGL((attend_partial_kernel<IT, D, ATTEND_MAX_ROWS>), grid, dim3(64),
-                       (attend_lds_bytes<IT, D>(ATTEND_MAX_ROWS)), st, a);
+    hipLaunchKernelGGL((attend_rows_kernel<IT, D, 32>), grid, dim3(64 * ATTEND_WAVES), (attend_lds_bytes<D, 32>()), st,
+                       a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((attend_merge_kernel<IT, D>), dim3(a.group * a.nq, a.H), dim3(64 * ATTEND_MERGE_WAVES), 0,

@@ -23,3 +23,41 @@ def test_refinement_rule_edge(mode, scale):
     from which the near-maximal logits are recomputed."""
     w = configs.shrink(configs.get_workload(1), logit_scale_cross=scale)
     _layer_case(w, mode, 1000, 130, f"cfg1 scale {scale} mode {mode}")
+
+
+def _attend_case(H, group, nq, t, S, d, causal, mode, rotate=False):
+    import numpy as np
+    import torch
+    from oracle import consumer
+    from paper_2606_07878_amd import binding
+    from tests.helpers import dev_tensor, log, slice_errors
+    a = synth.make_attend_inputs(7, H, group, nq, t, S, d, beta=t > 0)
+    f = synth.as_f64(a)
+    qpos = 5000.5 + np.arange(nq, dtype=np.float64) if rotate else None
+    ref = consumer.attend(f["q"], f["C_k"], f["C_v"], None if a["beta"] is None else a["beta"].astype(np.float64),
+                          f["K"], f["V"], group=group, causal=causal, q_positions=qpos, rope_theta=1e6)
+    dv = {k: (dev_tensor(v, mode) if v is not None else None) for k, v in a.items()}
+    out = binding.attend(dv["q"], dv["C_k"] if t else None, dv["C_v"] if t else None, dv["beta"] if t else None,
+                         dv["K"] if S else None, dv["V"] if S else None, group=group, causal=causal,
+                         q_positions=None if qpos is None else torch.from_numpy(qpos).cuda(), rope_theta=1e6)
+    torch.cuda.synchronize()
+    err = slice_errors(out.double().cpu().numpy(), ref).max()
+    tol = 8e-3 if mode == configs.MODE_BF16 else 1e-5   # the bf16 output's rounding; fp32 sums
+    log(f"attend H={H} group={group} nq={nq} t={t} S={S} d={d} causal={causal} mode={mode}: {err:.3e} (tol {tol:g})")
+    assert err <= tol
+
+
+@pytest.mark.parametrize("mode", [configs.MODE_BF16, configs.MODE_FP32])
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("group,nq,t,S,causal", [
+    (2, 1, 700, 9, False),     # 2 rows: the decode kernel at every width
+    (2, 2, 700, 5444, True),   # 4 rows over 2 x 6144 keys: decode kernel at widths 128 and 256
+    (2, 2, 700, 5445, True),   # ... over one key more: matrix kernel
+    (1, 3, 0, 65, True),       # 3 rows without a compact part
+    (3, 3, 31, 33, True),      # 9 rows in the 16-row tile; chunks of 32 cut short and spilling over by one
+    (4, 4, 0, 16, True),       # 16 rows: the last; fewer keys than one chunk, most of them masked for the first row
+    (1, 17, 129, 17, True),    # 17 rows: the first of the 32-row tile; five chunks, so one wave takes two
+    (4, 8, 4500, 0, False),    # 32 rows: the last; several splits, no suffix
+])
+def test_attend_row_tiles(mode, d, group, nq, t, S, causal):
+    _attend_case(2, group, nq, t, S, d, causal, mode, rotate=nq == 17)
