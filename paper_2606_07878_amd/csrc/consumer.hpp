@@ -24,6 +24,7 @@ constexpr int ATTEND_MAX_ROWS = 32;   // group * n_queries
 inline __host__ __device__ int attend_decode_rows(int d, int heads, long keys) {
   return d >= 128 && heads * keys <= 12288 ? 4 : 2;
 }
+constexpr int ATTEND_KC = 32;         // keys per chunk of the matrix kernel
 
 struct ConsumerArgs {
   const void* q;        // [H*group][nq][D]
