@@ -136,6 +136,13 @@ __host__ __device__ __forceinline__ long xtile_off(long h, long f, long n, long 
 // maximum are candidates for the exact-logit refinement of cross-attention.
 constexpr float REFINE_MARGIN = 10.f;
 
+// Candidate lists of the fp16 cross-attention per (split, latent row): one per
+// (wave, lane half) of its workgroup, each written by one lane, so that no
+// candidate is counted through shared memory and the lists do not depend on
+// the order of the waves.  A run of equal keys falls to one wave, so a list
+// holds far more than an even share of the in-margin keys.
+constexpr int XATT_NBK = 8, XATT_CAP = 512;
+
 template <class CT> __device__ __forceinline__ typename Mma<CT>::frag zero_frag() {
   typename Mma<CT>::frag z;
 #pragma unroll

@@ -110,8 +110,9 @@ constexpr int GEMM_BN = 128;   // column tile of every GEMM (two halves of 64 pa
 constexpr int ATT_TT = 128;    // latents per attention workgroup
 constexpr int ATT_NB = 64;     // keys per attention block
 constexpr int ATT_TOPK = 4;    // keys tracked per latent half-lane for logit refinement (fp32 kernel)
-constexpr int XATT_KB = 256;   // keys per block of the fp16 cross-attention kernel
-constexpr int XATT_TOPK = 4;   // keys tracked per (latent, wave, lane half) by the fp16 kernel
+// keys per block of the fp16 attention kernel for a value width d2 (attn.hpp:
+// the logit and output accumulators share the registers)
+constexpr int xatt_kb(int d2) { return d2 == 256 ? 512 : 256; }
 // keys per latent whose logits are recomputed accurately: every candidate
 // within the refinement margin, up to this many
 constexpr int REFINE_R = 256;
@@ -119,8 +120,6 @@ static_assert(REFINE_R <= REFINE_RMAX, "merge_kernel handles up to REFINE_RMAX r
 // refinement rows per list the fp16 refinement grid covers at once (its
 // workgroups loop over further tiles): about 4 per latent
 constexpr int REFINE_GRID_R = 4;
-// waves of the fp16 cross-attention workgroup for a value width d2 = 2d
-constexpr int xatt_waves(int) { return 4; }
 
 // ---------------------------------------------------------------------------
 // Derived dimensions and workspace layout
@@ -129,9 +128,9 @@ struct Dims {
   int H, d, D, d2, nc, dc, ns, ds, F, Ec, Es, t, tpad;
   long N, Npad;
   int np_c, np_s;       // sum-of-squares partials per (row, head)
-  int topk, R;          // logit refinement
-  int ncand;            // candidate slots per (split, latent row) written by the attention kernel
-  int ncand_fixed;      // ... of which the fixed lists (then up to ATT_OVF / XATT_OVF overflow entries)
+  int R;                // logit refinement
+  int ncand;            // fp32 mode: candidate slots per (split, latent row) written by the attention kernel
+  int ncand_fixed;      // ... of which the fixed lists (then up to ATT_OVF overflow entries)
   int att_tt;           // latents per attention workgroup
   int splits;           // split-N factor of the cross-attention
   long keys_per_split;
@@ -151,7 +150,7 @@ struct Plan {
   size_t wconv;          // bf16 mode: the layer's weight matrices converted to fp16
   size_t wkt;            // bf16 mode: fragment-tiled fp16 copy of the cross-attention W_K
   size_t X, XT, Z, Y, q, partq, rq, O;
-  size_t Ylo, qex, cval, cidx, ocnt, ridx, rval, rcnt, rpart, crow, ccount;   // logit refinement
+  size_t Ylo, qex, cval, cidx, cand, ocnt, ridx, rval, rcnt, rpart, crow, ccount;   // logit refinement
   size_t q64;                   // fp32 mode: fp64 queries of the refinement
   size_t invf_b, invf_c;        // fp64 RoPE frequencies (base, compactor)
   size_t kvpart, hscale;        // bf16 mode: per-head fp16 range scale of the staged cache
@@ -163,13 +162,34 @@ struct Plan {
   size_t total;
 };
 
-inline int key_block(const Dims& m) { return m.fp32 ? ATT_NB : XATT_KB; }
+inline int key_block(const Dims& m) { return m.fp32 ? ATT_NB : xatt_kb(m.d2); }
+
+// Key splits of the fp16 attention kernel (one workgroup per CU): the
+// workgroups run in rounds of 256, so the time is about rounds x (key blocks
+// per split + the start and end of a workgroup, about half a block of 256
+// keys); the fewest splits within 2 % of the best.
+inline int balanced_splits(long wgs, long nblocks, int kb) {
+  const double fixed = 128.0 / kb;
+  double best = 0;
+  long pick = 1;
+  for (long want = 1; want <= nblocks; ++want) {
+    const long per = (nblocks + want - 1) / want, s = (nblocks + per - 1) / per;
+    if (s != want) continue;   // the same blocks per split with fewer splits was looked at already
+    const double cost = (double)((wgs * s + 255) / 256) * ((double)per + fixed);
+    if (want == 1 || cost < best * 0.98) {
+      best = cost;
+      pick = s;
+    }
+    if (wgs * s >= 8 * 256) break;
+  }
+  return (int)pick;
+}
 
 inline int choose_splits(const Dims& m) {
   const long wgs = (long)((m.t + m.att_tt - 1) / m.att_tt) * m.H * m.nc;
   const long nblocks = (m.N + key_block(m) - 1) / key_block(m);
-  // fp16 kernel: one workgroup per CU, aim for >= 2 per CU; fp32: >= 4
-  long s = ((m.fp32 ? 1024 : 512) + wgs - 1) / wgs;
+  if (!m.fp32) return balanced_splits(wgs, nblocks, key_block(m));
+  long s = (1024 + wgs - 1) / wgs;   // fp32 kernel: at least 4 workgroups per CU
   if (s > nblocks) s = nblocks;
   if (s < 1) s = 1;
   return (int)s;
@@ -221,26 +241,23 @@ inline still_status make_dims(const still_config* c, int64_t N, int32_t t, Dims*
   m->Npad = rup(N, 256);
   m->np_c = m->dc / GEMM_BN * 2;
   m->np_s = m->ns > 0 ? m->ds / GEMM_BN * 2 : 0;
-  m->topk = m->fp32 ? ATT_TOPK : XATT_TOPK;
-  m->ncand_fixed = m->fp32 ? 2 * ATT_TOPK : 2 * xatt_waves(m->d2) * XATT_TOPK;
-  m->ncand = m->ncand_fixed + (m->fp32 ? ATT_OVF : XATT_OVF);
+  m->ncand_fixed = 2 * ATT_TOPK;
+  m->ncand = m->ncand_fixed + ATT_OVF;
   m->R = REFINE_R;
-  m->att_tt = (m->fp32 || m->d2 <= 256) ? 128 : 64;
+  m->att_tt = 128;
   m->splits = choose_splits(*m);
   m->keys_per_split = rup((m->N + m->splits - 1) / m->splits, key_block(*m));
   m->splits = (int)((m->N + m->keys_per_split - 1) / m->keys_per_split);
-  m->tpadk = (int)rup(t, XATT_KB);
+  m->tpadk = (int)rup(t, 256);
   m->sa_flash = !m->fp32 && m->ns > 0 && (m->ds == 128 || m->ds == 256 || m->ds == 512) &&
                 (double)m->tpadk * m->Es * 2.0 < 4294967296.0;
   m->sa_splits = 1;
   m->sa_kps = m->tpadk;
   if (m->sa_flash) {
-    const int tt = m->ds <= 256 ? 128 : 64;
-    const long wgs = (long)((t + tt - 1) / tt) * m->H * m->ns;
-    long s = (512 + wgs - 1) / wgs;
-    if (s > m->tpadk / XATT_KB) s = m->tpadk / XATT_KB;
-    if (s < 1) s = 1;
-    m->sa_kps = rup((t + s - 1) / s, XATT_KB);
+    const int kb = xatt_kb(m->ds);
+    const long wgs = (long)((t + 127) / 128) * m->H * m->ns;
+    const long sp = balanced_splits(wgs, (t + kb - 1) / kb, kb);
+    m->sa_kps = rup((t + sp - 1) / sp, kb);
     m->sa_splits = (int)((t + m->sa_kps - 1) / m->sa_kps);
   }
   return STILL_OK;
@@ -335,9 +352,14 @@ inline Plan make_plan(const still_config* c, const Dims& m) {
       p.Ylo = take(cs * Ht * m.D);
       p.qex = take(4ul * Ht * m.Ec);
     }
-    p.cval = take(4ul * m.splits * HCT * m.ncand);
-    p.cidx = take(4ul * m.splits * HCT * m.ncand);
-    p.ocnt = take(4ul * m.splits * HCT);
+    if (m.fp32) {
+      p.cval = take(4ul * m.splits * HCT * m.ncand);
+      p.cidx = take(4ul * m.splits * HCT * m.ncand);
+      p.ocnt = take(4ul * m.splits * HCT);
+    } else {
+      p.cand = take(8ul * m.splits * HCT * XATT_NBK * XATT_CAP);
+      p.ocnt = take(4ul * m.splits * HCT * XATT_NBK);
+    }
     p.ridx = take(4ul * HCT * m.R);
     p.rval = take(4ul * HCT * m.R);
     p.rcnt = take(4ul * HCT);
@@ -437,6 +459,10 @@ inline still_status check_layer(const still_config* c, const Dims& m, const stil
 #undef CHK
   return STILL_OK;
 }
+
+// The fp16 attention (xattn.hip) for value widths a.d2 of 128, 256 or 512;
+// track: list the candidates of the logit refinement.
+hipError_t launch_xattn_f16(const AttnArgs& a, bool track, int splits, hipStream_t st);
 
 // One layer of the compaction (layer.hpp); IT = I/O type of K, V, weights and
 // outputs, CT = MFMA operand / intermediate storage type.  Instantiated for

@@ -93,18 +93,14 @@ static GemmArgs gargs(int M, int N, int K, const void* A, long lda, const void* 
 }
 
 
-template <class CT, int D2, int TOPK = XATT_TOPK>
+// TRACK: candidates of the logit refinement (cross-attention)
+template <class CT, int D2, bool TRACK = true>
 static hipError_t launch_attn(const AttnArgs& a, int splits, hipStream_t st) {
-  dim3 grid((a.t + ATT_TT - 1) / ATT_TT, a.H * a.nc, splits);
-  if constexpr (sizeof(CT) == 2) {
-    constexpr int TT = D2 <= 256 ? 128 : 64;
-    const int ntt = (a.t + TT - 1) / TT;
-    static_assert(xatt_waves(D2) == 4, "the fp16 kernel runs 4 waves");
-    hipLaunchKernelGGL((xattn_f16_kernel<TT, D2, TOPK>), dim3(ntt * a.H * a.nc * splits), dim3(256), 0, st, a);
-  } else {
-    hipLaunchKernelGGL((cross_attn_kernel<CT, ATT_TT, (D2 > 256 ? 32 : ATT_NB), 32, D2, (TOPK > 0 ? ATT_TOPK : 0)>),
+  if constexpr (sizeof(CT) == 2) return launch_xattn_f16(a, TRACK, splits, st);
+  const dim3 grid((a.t + ATT_TT - 1) / ATT_TT, a.H * a.nc, splits);
+  if constexpr (sizeof(CT) == 4)
+    hipLaunchKernelGGL((cross_attn_kernel<CT, ATT_TT, (D2 > 256 ? 32 : ATT_NB), 32, D2, (TRACK ? ATT_TOPK : 0)>),
                        grid, dim3(256), 0, st, a);
-  }
   return hipGetLastError();
 }
 
@@ -342,8 +338,9 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
         a.d2 = m.d2;
         a.scale_log2 = ca_scale * LOG2E;
         a.keys_per_split = (int)m.keys_per_split;
-        a.cval = (float*)(ws + p.cval);
-        a.cidx = (int*)(ws + p.cidx);
+        a.cval = m.fp32 ? (float*)(ws + p.cval) : nullptr;
+        a.cidx = m.fp32 ? (int*)(ws + p.cidx) : nullptr;
+        a.cand = m.fp32 ? nullptr : (float2*)(ws + p.cand);
         a.ocnt = (int*)(ws + p.ocnt);
         a.xfeat = m.d2;
         a.xcoff = 0;
@@ -351,9 +348,9 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
         {
         TIMED(STILL_K_CROSS_ATTN);
         if (!refine) {
-          if (m.d2 == 128) e = launch_attn<CT, 128, 0>(a, m.splits, st);
-          else if (m.d2 == 256) e = launch_attn<CT, 256, 0>(a, m.splits, st);
-          else e = launch_attn<CT, 512, 0>(a, m.splits, st);
+          if (m.d2 == 128) e = launch_attn<CT, 128, false>(a, m.splits, st);
+          else if (m.d2 == 256) e = launch_attn<CT, 256, false>(a, m.splits, st);
+          else e = launch_attn<CT, 512, false>(a, m.splits, st);
         } else if (m.d2 == 128) e = launch_attn<CT, 128>(a, m.splits, st);
         else if (m.d2 == 256) e = launch_attn<CT, 256>(a, m.splits, st);
         else e = launch_attn<CT, 512>(a, m.splits, st);
@@ -369,9 +366,16 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
           int* ccount = (int*)(ws + p.ccount);
           {
             TIMED(STILL_K_REFINE);
-            hipLaunchKernelGGL((refine_select_kernel<REFINE_R>), dim3((unsigned)((HCT + 3) / 4)), dim3(256), 0,
-                               st, a.cval, a.cidx, a.ocnt, a.mpart, m.splits, HCT, m.ncand, m.ncand_fixed, ridx,
-                               (float*)(ws + p.rval), (int*)(ws + p.rcnt));
+            CandArgs ca;
+            ca.cval = a.cval;
+            ca.cidx = a.cidx;
+            ca.cand = a.cand;
+            ca.cnt = a.ocnt;
+            ca.C = m.ncand;
+            ca.CB = m.ncand_fixed;
+            hipLaunchKernelGGL((refine_select_kernel<REFINE_R, sizeof(CT) == 2>), dim3((unsigned)((HCT + 3) / 4)),
+                               dim3(256), 0, st, ca, a.mpart, m.splits, HCT, ridx, (float*)(ws + p.rval),
+                               (int*)(ws + p.rcnt));
             HIP_TRY(hipGetLastError());
             hipLaunchKernelGGL(refine_compact_kernel, dim3(NB), dim3(256), 0, st, (const int*)(ws + p.rcnt), m.t,
                                m.R, crow, ccount);
@@ -581,9 +585,9 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
         {
           TIMED(STILL_K_LATENT);
           hipError_t e;
-          if (m.ds == 128) e = launch_attn<CT, 128, 0>(a, m.sa_splits, st);
-          else if (m.ds == 256) e = launch_attn<CT, 256, 0>(a, m.sa_splits, st);
-          else e = launch_attn<CT, 512, 0>(a, m.sa_splits, st);
+          if (m.ds == 128) e = launch_attn<CT, 128, false>(a, m.sa_splits, st);
+          else if (m.ds == 256) e = launch_attn<CT, 256, false>(a, m.sa_splits, st);
+          else e = launch_attn<CT, 512, false>(a, m.sa_splits, st);
           HIP_TRY(e);
           const dim3 mg((unsigned)((Ht * m.ns + 3) / 4));
           if (m.ds == 128)

@@ -440,26 +440,32 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(const float* __restri
 // 2^-REFINE_MARGIN of the row maximum.
 // ---------------------------------------------------------------------------
 
-// Pick, per latent row, every candidate of the flash pass's per-split lists
-// whose logit lies within REFINE_MARGIN of the row maximum, largest first, up
-// to R of them: slots [0, rcnt[row]) of the row hold them.  Exact ties (duplicated
-// cache rows) are taken together up to that cap, so their weights stay
-// consistent.  More than CAP in-margin entries in a row: the first CAP read
-// are ranked.  A split's
-// list of C entries holds CB fixed entries, then (with ocnt) ocnt[split][row]
-// overflow entries.
+// The candidate lists of the flash pass, per (split, latent row): fp32 kernel
+// C entries, CB fixed ones then cnt[split][row] overflow entries; fp16 kernel
+// XATT_NBK lists of up to XATT_CAP (logit, key) pairs, cnt[split][row][list]
+// of them filled.
+struct CandArgs {
+  const float* cval;
+  const int* cidx;
+  const float2* cand;
+  const int* cnt;
+  int C, CB;
+};
+
+// Pick, per latent row, every candidate of those lists whose logit lies
+// within REFINE_MARGIN of the row maximum, largest first, up to R of them:
+// slots [0, rcnt[row]) of the row hold them.  Exact ties (duplicated cache
+// rows) are taken together up to that cap, so their weights stay consistent.
+// More than CAP in-margin entries in a row: the first CAP read are ranked.
 //
-// One wave per row: the lists are read with coalesced loads, the in-margin
-// candidates (usually two or three) are compacted into LDS, and each takes
-// its rank among them, equal logits ordered by key index, so the selection
-// does not depend on the order in which the flash pass appended overflow
-// entries.
-template <int R>
-__global__ __launch_bounds__(256) void refine_select_kernel(const float* __restrict__ cval,
-                                                            const int* __restrict__ cidx,
-                                                            const int* __restrict__ ocnt,
-                                                            const float* __restrict__ mpart, int S, long HCT, int C,
-                                                            int CB, int* __restrict__ ridx, float* __restrict__ rval,
+// One wave per row: the lists are read with coalesced loads (LISTS: 8 entries
+// of each list per step), the in-margin candidates (usually two or three) are
+// compacted into LDS, and each takes its rank among them, equal logits
+// ordered by key index, so the selection does not depend on the order in
+// which the fp32 flash pass appended overflow entries.
+template <int R, bool LISTS>
+__global__ __launch_bounds__(256) void refine_select_kernel(CandArgs ca, const float* __restrict__ mpart, int S,
+                                                            long HCT, int* __restrict__ ridx, float* __restrict__ rval,
                                                             int* __restrict__ rcnt) {
   constexpr int CAP = 512;   // in-margin candidates kept per row
   __shared__ float sv[4][CAP];
@@ -476,15 +482,21 @@ __global__ __launch_bounds__(256) void refine_select_kernel(const float* __restr
   int n = 0;
   if (active) {
     for (int s = 0; s < S; ++s) {
-      const long base = (s * HCT + row) * C;
-      const int cnt = CB + (ocnt ? ocnt[s * HCT + row] : 0);
-      for (int k0 = 0; k0 < cnt; k0 += 64) {
-        const int k = k0 + lane;
+      const long sr = s * HCT + row;
+      const int list = lane >> 3, cnt = LISTS ? ca.cnt[sr * XATT_NBK + list] : ca.CB + ca.cnt[sr];
+      for (int k0 = 0; __any(k0 < cnt); k0 += LISTS ? 8 : 64) {
+        const int k = k0 + (LISTS ? lane & 7 : lane);
         float v = -INFINITY;
         int id = -1;
         if (k < cnt) {
-          v = cval[base + k];
-          id = cidx[base + k];
+          if constexpr (LISTS) {
+            const float2 e = ca.cand[(sr * XATT_NBK + list) * XATT_CAP + k];
+            v = e.x;
+            id = __float_as_int(e.y);
+          } else {
+            v = ca.cval[sr * ca.C + k];
+            id = ca.cidx[sr * ca.C + k];
+          }
         }
         const bool keep = id >= 0 && v >= cut;
         const unsigned long long mask = __ballot(keep);

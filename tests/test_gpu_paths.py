@@ -61,3 +61,28 @@ def _attend_case(H, group, nq, t, S, d, causal, mode, rotate=False):
 ])
 def test_attend_row_tiles(mode, d, group, nq, t, S, causal):
     _attend_case(2, group, nq, t, S, d, causal, mode, rotate=nq == 17)
+
+
+@pytest.mark.parametrize("d,N,t", [
+    (128, 1, 1), (128, 256, 128), (128, 257, 129),       # one block of 512 keys, partly past the padded keys
+    (128, 512, 127), (128, 513, 130), (128, 769, 64),    # one whole block; one key into the second; past its half
+    (128, 4700, 300),                                    # several key splits, the last one short
+    (256, 255, 33), (256, 257, 129), (256, 1500, 260),   # blocks of 256 keys, 512 value features
+])
+def test_attention_blocks(d, N, t):
+    w = configs.shrink(configs.get_workload(1), head_dim=d, n_kv_heads=2)
+    _layer_case(w, configs.MODE_BF16, N, t, f"cfg1 d={d} N={N} t={t}")
+
+
+def test_attention_candidates_of_equal_keys():
+    """The same 100 tokens 41 times over (4100 keys): every latent's best key is
+    there 41 times, and more near-maximal ones, over two splits' lists."""
+    import numpy as np
+    w = configs.shrink(configs.get_workload(1), head_dim=128, n_kv_heads=2, n_tokens=4100, t=40)
+    base = synth.make_cache(w, 0, n_tokens=100)
+    cache = dict(K=np.tile(base["K"], (1, 41, 1)), V=np.tile(base["V"], (1, 41, 1)),
+                 positions=np.tile(base["positions"], 41))
+    wts = synth.make_weights(w, 0)
+    ref = run_oracle(w.cfg, cache, wts, w.rope_theta, 40)
+    got = run_gpu(w.cfg, cache, wts, w.rope_theta, 40)
+    assert_parity(got, ref, BF16_TOL, "41-fold keys")
