@@ -3,6 +3,7 @@
 // logit refinement, split merge, value and output projections), latent
 // self-attention, FFN and the output heads.
 #pragma once
+#include "bwd.hpp"
 #include "gemm.hpp"
 #include "host.hpp"
 #include "kproj.hpp"
@@ -60,8 +61,9 @@ static hipError_t gemm(const GemmArgs& g, int batch, hipStream_t st, int cls = S
     const long ntm = g.mgroups > 1 ? (g.M / g.mgroups + 128 / g.mgroups - 1) / (128 / g.mgroups) : (g.M + 127) / 128;
     if (PAIRED || ntn * ntm * batch >= 512) return launch_pick<CT, TA, TB, TC, TBias, EPI, 128, 256, 32>(g, batch, st);
   }
-  if constexpr (sizeof(CT) == 2) {
-    // fewer 128-row tiles than CUs (the output heads, small t): 64-row tiles
+  {
+    // fewer 128-row tiles than CUs (the output heads, small t): 64-row tiles.
+    // fp32, 2048 x 1024 x 8192: 128 tiles 562 us, 256 of half the rows 316 us
     constexpr bool PAIRED = (EPI == EPI_PAIR || EPI == EPI_SWIGLU);
     const long ntn = PAIRED ? (g.N + 63) / 64 : (g.N + 127) / 128;
     const long ntm = g.mgroups > 1 ? (g.M / g.mgroups + 128 / g.mgroups - 1) / (128 / g.mgroups) : (g.M + 127) / 128;
@@ -413,20 +415,28 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
             } else {
               // fp32 mode: the refined keys' logits in fp64 (refine64.hpp)
               double* q64 = (double*)(ws + p.q64);
-              Q64Args qa;
-              qa.Z = Z;
-              qa.W = (const float*)bw.ca_wq;
-              qa.bias = (const float*)bw.ca_bq;
-              qa.Q = q64;
-              qa.rows = Ht;
-              qa.D = m.D;
-              qa.E = m.Ec;
-              qa.rms_eps = cfg->rms_eps;
-              hipLaunchKernelGGL(q64_gemm_kernel, dim3((unsigned)((m.Ec + 127) / 128), (unsigned)((Ht + 127) / 128)),
-                                 dim3(256), 0, st, qa);
-              HIP_TRY(hipGetLastError());
+              // q64 = Z W_Q^T (the RMS factor, the bias and the rotation follow in the finalisation)
+              SgemmArgs qg;
+              memset(&qg, 0, sizeof qg);
+              qg.am = m.D;
+              qg.ak = 1;
+              qg.bn = m.D;
+              qg.bk = 1;
+              qg.ldc = m.Ec;
+              qg.N = m.Ec;
+              qg.K = m.D;
+              qg.nb2 = 1;
+              qg.alpha = 1.f;
+              for (long r0 = 0; r0 < Ht; r0 += 64L * 65535) {   // (grid rows are limited to 65535)
+                qg.M = (int)std::min(Ht - r0, 64L * 65535);
+                hipLaunchKernelGGL((dgemm_kernel<true, true, float, float, double>),
+                                   dim3((unsigned)((m.Ec + 63) / 64), (unsigned)((qg.M + 63) / 64)), dim3(256), 0, st,
+                                   qg, (const float*)Z + r0 * m.D, (const float*)bw.ca_wq, q64 + r0 * m.Ec);
+                HIP_TRY(hipGetLastError());
+              }
               hipLaunchKernelGGL(q64_finalize_kernel, dim3((unsigned)((Ht * m.nc + 3) / 4)), dim3(256), 0, st, q64,
-                                 Ht, m.nc, m.dc, m.t, (const double*)(ws + p.pq), (const double*)(ws + p.invf_c),
+                                 (const float*)Z, (const float*)bw.ca_bq, Ht, m.nc, m.dc, m.D, m.t,
+                                 (const double*)(ws + p.pq), (const double*)(ws + p.invf_c), (double)cfg->rms_eps,
                                  (double)cfg->l2_eps);
               HIP_TRY(hipGetLastError());
               Refine64Args r6;
@@ -452,7 +462,8 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
               r6.d = m.d;
               r6.scale_log2 = (double)ca_scale * 1.4426950408889634;
               r6.l2_eps = (double)cfg->l2_eps;
-              r6.ntile = (m.t * REFINE_GRID_R + 15) / 16;
+              const int bm6 = m.d > 128 ? 16 : 32;   // candidate rows per workgroup (refine64_kernel)
+              r6.ntile = (m.t * REFINE_GRID_R + bm6 - 1) / bm6;
               const dim3 rg((unsigned)(r6.ntile * NB));
               if (m.d == 64) hipLaunchKernelGGL((refine64_kernel<64>), rg, dim3(256), 0, st, r6);
               else if (m.d == 128) hipLaunchKernelGGL((refine64_kernel<128>), rg, dim3(256), 0, st, r6);

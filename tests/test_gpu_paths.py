@@ -86,3 +86,10 @@ def test_attention_candidates_of_equal_keys():
     ref = run_oracle(w.cfg, cache, wts, w.rope_theta, 40)
     got = run_gpu(w.cfg, cache, wts, w.rope_theta, 40)
     assert_parity(got, ref, BF16_TOL, "41-fold keys")
+
+
+@pytest.mark.parametrize("d,N,t", [(64, 65, 17), (128, 300, 33), (128, 40, 1), (256, 257, 15), (256, 700, 49)])
+def test_fp64_refinement_tiles(d, N, t):
+    """fp32 mode: candidate lists that fill 32-row (16-row at d = 256) tiles in part."""
+    w = configs.shrink(configs.get_workload(1), head_dim=d, n_kv_heads=2)
+    _layer_case(w, configs.MODE_FP32, N, t, f"cfg1 fp32 d={d} N={N} t={t}")
