@@ -168,7 +168,8 @@ __global__ __launch_bounds__(64 * ATTEND_WAVES) void attend_rows_kernel(Consumer
   constexpr int ROWB = D * (int)sizeof(IT), EPP = 16 / (int)sizeof(IT), NP = ROWB / 16 / LG;
   constexpr int FPT = D / TR, VB = FPT * (int)sizeof(IT), LQ = D + 4;
   constexpr bool AHEAD = ROWB <= 512;
-  static_assert(NP >= 1 && NKT >= 1 && CR % 4 == 0, "tile shape");
+  constexpr int NA0 = TR == 16 ? 8 : 4, NA = NP < NA0 ? NP : NA0;   // partial sums of a logit
+  static_assert(NP >= NA && NKT >= 1 && CR % 4 == 0, "tile shape");
   extern __shared__ float4 attend_smem[];
   float* qs = (float*)attend_smem;                     // [TR][LQ]
   float* kbias = qs + TR * LQ;                         // [waves][KC]: bias of a chunk's keys
@@ -251,12 +252,14 @@ __global__ __launch_bounds__(64 * ATTEND_WAVES) void attend_rows_kernel(Consumer
       load_k(ch);
       bias = load_bias(ch);
     }
-    // ---- logits
-    typename MM::acc s[NKT];
+    // ---- logits, summed in NA parts (shorter chains of fp32 additions)
+    typename MM::acc s[NKT], sp[NKT][NA];
 #pragma unroll
     for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
-      for (int j = 0; j < CR; ++j) s[kt][j] = 0.f;
+      for (int q = 0; q < NA; ++q)
+#pragma unroll
+        for (int j = 0; j < CR; ++j) sp[kt][q][j] = 0.f;
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
       float qv[EPP];
@@ -273,9 +276,20 @@ __global__ __launch_bounds__(64 * ATTEND_WAVES) void attend_rows_kernel(Consumer
         float kv[EPP];
         unpack16<IT>(kp[kt][i], kv);
 #pragma unroll
-        for (int e = 0; e < EPP; ++e) MM::mma(s[kt], kv[e], qv[e]);
+        for (int e = 0; e < EPP; ++e) MM::mma(sp[kt][i * NA / NP], kv[e], qv[e]);
       }
     }
+#pragma unroll
+    for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+      for (int j = 0; j < CR; ++j)
+      {
+#pragma unroll
+        for (int st = 1; st < NA; st *= 2)
+#pragma unroll
+          for (int q = 0; q + st < NA; q += 2 * st) sp[kt][q][j] += sp[kt][q + st][j];
+        s[kt][j] = sp[kt][0][j];
+      }
     if (lane < KC) kbias[w * KC + lane] = bias;   // (this wave's slot; read back below in program order)
     if constexpr (AHEAD) {
       if (c + ATTEND_WAVES < c1) {
@@ -320,19 +334,25 @@ __global__ __launch_bounds__(64 * ATTEND_WAVES) void attend_rows_kernel(Consumer
     const float al = expf(m - mref);
     ls = ls * al + cs;
     m = mn;
-    if (__any(al != 1.f)) {
+    // ---- P.V of the chunk, half of its keys in each of two sums, then added
+    // to the running (rescaled) sums: chains of 16 keys, not of all keys
 #pragma unroll
-      for (int f = 0; f < FPT; ++f)
+    for (int f = 0; f < FPT; ++f) {
+      typename MM::acc pv[2];
 #pragma unroll
-        for (int j = 0; j < CR; ++j) o[f][j] *= al;
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int j = 0; j < CR; ++j) pv[q][j] = 0.f;
+#pragma unroll
+      for (int i = 0; i < NKT * CR / 2; ++i)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int x = q * (NKT * CR / 2) + i;
+          MM::mma(pv[q], word_elem<IT>(vr[x], f), s[x / CR][x % CR]);
+        }
+#pragma unroll
+      for (int j = 0; j < CR; ++j) o[f][j] = fmaf(o[f][j], al, pv[0][j] + pv[1][j]);
     }
-    // ---- P.V
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-      for (int j = 0; j < CR; ++j)
-#pragma unroll
-        for (int f = 0; f < FPT; ++f) MM::mma(o[f], word_elem<IT>(vr[kt * CR + j], f), s[kt][j]);
   }
   // ---- combine the waves (each lane holds its row's m, l and features l' FPT + f,
   // l' = row(j, lg) of the accumulator) and write the split's partial rows
