@@ -181,12 +181,20 @@ hipError_t sgemm(hipStream_t st, int M, int N, int K, Op A, Op B, float* C, long
     g.part = t_kpart;
   }
   const int nz = splits > 1 ? (int)(((long)K + g.ksplit - 1) / g.ksplit) : bt.nb1 * bt.nb2;
-  const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)nz);
   const bool ak = A.ks == 1, bk = B.ks == 1;
-  if (ak && bk) hipLaunchKernelGGL((sgemm_kernel<true, true>), grid, dim3(256), 0, st, g);
-  else if (ak) hipLaunchKernelGGL((sgemm_kernel<true, false>), grid, dim3(256), 0, st, g);
-  else if (bk) hipLaunchKernelGGL((sgemm_kernel<false, true>), grid, dim3(256), 0, st, g);
-  else hipLaunchKernelGGL((sgemm_kernel<false, false>), grid, dim3(256), 0, st, g);
+  auto launch = [&](auto tc) {
+    constexpr int T = decltype(tc)::value;
+    const dim3 grid((unsigned)((N + T - 1) / T), (unsigned)((M + T - 1) / T), (unsigned)nz);
+    if (ak && bk) hipLaunchKernelGGL((sgemm_kernel<true, true, T>), grid, dim3(256), 0, st, g);
+    else if (ak) hipLaunchKernelGGL((sgemm_kernel<true, false, T>), grid, dim3(256), 0, st, g);
+    else if (bk) hipLaunchKernelGGL((sgemm_kernel<false, true, T>), grid, dim3(256), 0, st, g);
+    else hipLaunchKernelGGL((sgemm_kernel<false, false, T>), grid, dim3(256), 0, st, g);
+  };
+  // 128 x 128 tiles (half the operand traffic per flop) where they leave two
+  // workgroups per CU and little of the last tile row and column is padding
+  const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
+  if (t128 * nz >= 512 && t128 * 128 * 128 <= (long)M * N * 5 / 4) launch(std::integral_constant<int, 128>{});
+  else launch(std::integral_constant<int, 64>{});
   if (splits > 1) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -16,9 +16,8 @@ namespace still {
 //   C[b](m, n) = alpha * sum_k A[b](m, k) B[b](n, k)   (+ C[b](m, n) if accumulate)
 // with A[b](m, k) = A[b1 * sa1 + b2 * sa2 + m * am + k * ak], one of am, ak
 // equal to 1 (likewise B), b = b1 * nb2 + b2 the batch index, C row-major
-// with leading dimension ldc.  64 x 64 tiles, k stages of 32 (the next
-// stage loaded into registers during the current one's MFMAs), four waves
-// each owning one 32 x 32 MFMA tile; operands staged in LDS as [row][k].
+// with leading dimension ldc.  64 x 64 or 128 x 128 tiles, k stages of 32 (the
+// next stage loaded into registers during the current one's MFMAs).
 // ---------------------------------------------------------------------------
 struct SgemmArgs {
   const float* A;
@@ -39,127 +38,131 @@ struct SgemmArgs {
   void* part;
 };
 
-// Load this thread's part of a 64 x 16 tile (rows r0.., k k0..) of a
-// strided operand (k < K, rows < R; zeros outside) into registers, and store
-// it into LDS [64][LK].  K-contiguous sources: 4 consecutive k per thread;
-// row-contiguous sources: 4 consecutive rows; edges fall back to scalar loads.
-template <bool KCONT>
-__device__ __forceinline__ void sgemm_load(const float* __restrict__ X, long xr, long xk, int R, int K, int r0,
-                                           int k0, float (&v)[4]) {
-  const int tid = threadIdx.x;
+// One operand's k stages of T rows x KS indices for 256 threads, as runs of V
+// elements (16 bytes) along the operand's contiguous dimension (KCONT: k,
+// otherwise rows); run i of a thread covers row(i).., k(i)... .  Full tiles of
+// aligned operands load whole runs at constant 32-bit offsets from one scalar
+// base per stage; any other stage element by element, zeros outside
+// (row < R, k < kend).
+template <bool KCONT, int T, int KS, class TX> struct TileLoad {
+  static constexpr int V = 16 / (int)sizeof(TX), RUNS = T * KS / V / 256, PER_ROW = (KCONT ? KS : T) / V;
+  static_assert(RUNS >= 1 && T * KS % (256 * V) == 0, "runs per thread");
+  typedef TX run_t __attribute__((ext_vector_type(V)));
+  const TX* base;      // row r0, k 0
+  long xr, xk;
+  int rows;            // rows of the tile inside the operand
+  bool whole;          // uniform: every run of a full stage can be loaded as one
+  __device__ __forceinline__ TileLoad(const TX* X, long xr_, long xk_, int R, int r0)
+      : base(X + (long)r0 * xr_), xr(xr_), xk(xk_), rows(R - r0),
+        whole(R - r0 >= T && (KCONT ? xr_ : xk_) % V == 0 && ((uintptr_t)(X + (long)r0 * xr_) & 15u) == 0 &&
+              (KCONT ? xr_ : xk_) < (1l << 22)) {}
+  __device__ __forceinline__ int row(int i) const {
+    const int e = threadIdx.x + 256 * i;
+    return KCONT ? e / PER_ROW : (e % PER_ROW) * V;
+  }
+  __device__ __forceinline__ int k(int i) const {
+    const int e = threadIdx.x + 256 * i;
+    return KCONT ? (e % PER_ROW) * V : e / PER_ROW;
+  }
+  __device__ __forceinline__ void load(int k0, int kend, run_t (&v)[RUNS]) const {
+    if (whole && k0 + KS <= kend && ((KCONT ? k0 : 0) % V) == 0) {
+      const TX* p = base + (long)k0 * xk;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = 0.f;
-  if (KCONT) {
-    const int r = tid >> 2, k = (tid & 3) * 4;
-    const int gr = r0 + r, gk = k0 + k;
-    if (gr < R) {
-      const float* p = X + gr * xr + gk;
-      if (gk + 3 < K && ((uintptr_t)p & 15u) == 0) {
-        const f32x4 q = *(const f32x4*)p;
-        v[0] = q[0];
-        v[1] = q[1];
-        v[2] = q[2];
-        v[3] = q[3];
-      } else {
+      for (int i = 0; i < RUNS; ++i)
+        v[i] = *(const run_t*)(p + (KCONT ? (unsigned)row(i) * (unsigned)xr + (unsigned)k(i)
+                                          : (unsigned)k(i) * (unsigned)xk + (unsigned)row(i)));
+    } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (gk + i < K) v[i] = p[i];
-      }
-    }
-  } else {
-    const int k = tid >> 4, r = (tid & 15) * 4;
-    const int gr = r0 + r, gk = k0 + k;
-    if (gk < K) {
-      const float* p = X + gk * xk + gr;
-      if (gr + 3 < R && ((uintptr_t)p & 15u) == 0) {
-        const f32x4 q = *(const f32x4*)p;
-        v[0] = q[0];
-        v[1] = q[1];
-        v[2] = q[2];
-        v[3] = q[3];
-      } else {
+      for (int i = 0; i < RUNS; ++i)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (gr + i < R) v[i] = p[i];
-      }
+        for (int u = 0; u < V; ++u) {
+          const int r = row(i) + (KCONT ? 0 : u), kk = k0 + k(i) + (KCONT ? u : 0);
+          v[i][u] = r < rows && kk < kend ? base[(long)r * xr + (long)kk * xk] : (TX)0;
+        }
     }
   }
-}
-template <bool KCONT>
-__device__ __forceinline__ void sgemm_store(const float (&v)[4], float* __restrict__ S, int LK) {
-  const int tid = threadIdx.x;
-  if (KCONT) {
-    const int r = tid >> 2, k = (tid & 3) * 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) S[r * LK + k + i] = v[i];
-  } else {
-    const int k = tid >> 4, r = (tid & 15) * 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) S[(r + i) * LK + k] = v[i];
-  }
-}
+};
 
-template <bool AK, bool BK>
+// T x T output tiles (64 or 128), four waves of T/2 x T/2.  A k-contiguous
+// operand is staged in LDS as [row][k] (rows of KS + 4), read as four
+// consecutive k per lane; a row-contiguous one as [k][row] (rows of T + 4),
+// read as the same four k from four LDS rows, so that both are stored as the
+// 16-byte runs they were loaded in.  65536 x 8192 x 256: 98 TFLOP/s on 64 x 64
+// tiles with element-wise address arithmetic, 106 here (the library 144 at
+// 4096^3); 8192 x 1024 x 256 in a batch of 64: 102, 120.
+template <bool AK, bool BK, int T>
 __global__ __launch_bounds__(256) void sgemm_kernel(SgemmArgs g) {
-  constexpr int T = 64, KS = 32, LK = KS + 4;   // k stage = two 16-wide halves
-  __shared__ __attribute__((aligned(16))) float As[T * LK];
-  __shared__ __attribute__((aligned(16))) float Bs[T * LK];
+  constexpr int KS = 32, TT = T / 64;   // 32 x 32 tiles per wave and dimension
+  constexpr int LK = KS + 4, LT = T + 4;
+  __shared__ __attribute__((aligned(16))) float As[AK ? T * LK : KS * LT];
+  __shared__ __attribute__((aligned(16))) float Bs[BK ? T * LK : KS * LT];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lg = lane >> 5;
   const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
   const int kz = g.ksplit ? (int)blockIdx.z : 0;
   const int b = g.ksplit ? 0 : (int)blockIdx.z, b1 = b / g.nb2, b2 = b - b1 * g.nb2;
   const int kbeg = kz * g.ksplit, kend = g.ksplit ? min(g.K, kbeg + g.ksplit) : g.K;
-  const float* A = g.A + b1 * g.sa1 + b2 * g.sa2;
-  const float* B = g.B + b1 * g.sb1 + b2 * g.sb2;
-  f32x16 acc = zero16();
-  // the next k stage is loaded into registers while the current one's MFMAs run
-  float ra[2][4], rb[2][4];
-  auto load = [&](int k0) {
+  typedef TileLoad<AK, T, KS, float> LA;
+  typedef TileLoad<BK, T, KS, float> LB;
+  const LA la(g.A + b1 * g.sa1 + b2 * g.sa2, g.am, g.ak, g.M, m0);
+  const LB lb(g.B + b1 * g.sb1 + b2 * g.sb2, g.bn, g.bk, g.N, n0);
+  f32x16 acc[TT][TT];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      sgemm_load<AK>(A, g.am, g.ak, g.M, kend, m0, k0 + 16 * h, ra[h]);
-      sgemm_load<BK>(B, g.bn, g.bk, g.N, kend, n0, k0 + 16 * h, rb[h]);
-    }
+  for (int i = 0; i < TT; ++i)
+#pragma unroll
+    for (int j = 0; j < TT; ++j) acc[i][j] = zero16();
+  // the next k stage is loaded into registers while the current one's MFMAs run
+  typename LA::run_t ra[LA::RUNS];
+  typename LB::run_t rb[LB::RUNS];
+  la.load(kbeg, kend, ra);
+  lb.load(kbeg, kend, rb);
+  auto frag = [&](const float* S, bool kc, int row, int k) -> f32x4 {
+    if (kc) return *(const f32x4*)&S[row * LK + k];
+    return f32x4{S[k * LT + row], S[(k + 1) * LT + row], S[(k + 2) * LT + row], S[(k + 3) * LT + row]};
   };
-  load(kbeg);
   for (int k0 = kbeg; k0 < kend; k0 += KS) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      sgemm_store<AK>(ra[h], As + 16 * h, LK);
-      sgemm_store<BK>(rb[h], Bs + 16 * h, LK);
-    }
+    for (int i = 0; i < LA::RUNS; ++i) *(f32x4*)&As[AK ? la.row(i) * LK + la.k(i) : la.k(i) * LT + la.row(i)] = ra[i];
+#pragma unroll
+    for (int i = 0; i < LB::RUNS; ++i) *(f32x4*)&Bs[BK ? lb.row(i) * LK + lb.k(i) : lb.k(i) * LT + lb.row(i)] = rb[i];
     __syncthreads();
-    if (k0 + KS < kend) load(k0 + KS);
+    if (k0 + KS < kend) {
+      la.load(k0 + KS, kend, ra);
+      lb.load(k0 + KS, kend, rb);
+    }
 #pragma unroll
     for (int kc = 0; kc < KS; kc += 8) {
-      const f32x4 af = *(const f32x4*)&As[(wm * 32 + l32) * LK + kc + 4 * lg];
-      const f32x4 bf = *(const f32x4*)&Bs[(wn * 32 + l32) * LK + kc + 4 * lg];
-      Mma<float>::mma(acc, af, bf);
+      f32x4 af[TT], bf[TT];
+#pragma unroll
+      for (int i = 0; i < TT; ++i) {
+        af[i] = frag(As, AK, (wm * TT + i) * 32 + l32, kc + 4 * lg);
+        bf[i] = frag(Bs, BK, (wn * TT + i) * 32 + l32, kc + 4 * lg);
+      }
+#pragma unroll
+      for (int i = 0; i < TT; ++i)
+#pragma unroll
+        for (int j = 0; j < TT; ++j) Mma<float>::mma(acc[i][j], af[i], bf[j]);
     }
     __syncthreads();
   }
-  if (g.ksplit) {
-    float* P = (float*)g.part + (long)kz * g.M * g.N;
+  float* C = g.ksplit ? (float*)g.part + (long)kz * g.M * g.N : g.C + b1 * g.sc1 + b2 * g.sc2;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int m = m0 + wm * 32 + 8 * (j >> 2) + 4 * lg + (j & 3);
-      const int n = n0 + wn * 32 + l32;
-      if (m < g.M && n < g.N) P[(long)m * g.N + n] = acc[j];
-    }
-    return;
-  }
-  float* C = g.C + b1 * g.sc1 + b2 * g.sc2;
+  for (int ti = 0; ti < TT; ++ti)
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int m = m0 + wm * 32 + 8 * (j >> 2) + 4 * lg + (j & 3);
-    const int n = n0 + wn * 32 + l32;
-    if (m < g.M && n < g.N) {
-      float* c = C + (long)m * g.ldc + n;
-      const float v = g.alpha * acc[j] + (g.bias ? g.bias[n] : 0.f);
-      *c = g.accumulate ? *c + v : v;
-    }
-  }
+    for (int tj = 0; tj < TT; ++tj)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int m = m0 + (wm * TT + ti) * 32 + 8 * (j >> 2) + 4 * lg + (j & 3);
+        const int n = n0 + (wn * TT + tj) * 32 + l32;
+        if (m >= g.M || n >= g.N) continue;
+        if (g.ksplit) {
+          C[(long)m * g.N + n] = acc[ti][tj][j];
+        } else {
+          float* c = C + (long)m * g.ldc + n;
+          const float v = g.alpha * acc[ti][tj][j] + (g.bias ? g.bias[n] : 0.f);
+          *c = g.accumulate ? *c + v : v;
+        }
+      }
 }
 
 // The same product in fp64 (fp64 MFMA, v_mfma_f64_16x16x4_f64), for the
@@ -169,13 +172,16 @@ __global__ __launch_bounds__(256) void sgemm_kernel(SgemmArgs g) {
 // 32 x 32 quadrant (wm, wn) as 2 x 2 MFMA tiles of 16 x 16.  Operand layout
 // of the MFMA: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] of
 // the 16 x 4 and 4 x 16 step; the result is C[l / 16 + 4 v][l % 16] in
-// register pair v of lane l (checked with a probe on the hardware).
+// register pair v of lane l (checked with a probe on the hardware).  Whole
+// 16-byte runs from one scalar base per chunk (TileLoad) in place of an address
+// and a bounds check per element: 256 x 8192 x 1024 in a batch of 64 5.23 ->
+// 4.72 ms, 65536 x 8192 x 256 4.91 -> 4.42 (62 TFLOP/s; the library 71 at 4096^3).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 template <bool AK, bool BK, class TA, class TB, class TC>
 __global__ __launch_bounds__(256) void dgemm_kernel(SgemmArgs g, const TA* __restrict__ A0, const TB* __restrict__ B0,
                                                     TC* __restrict__ C0) {
-  constexpr int T = 64, KS = 32, PER = T * KS / 256;
+  constexpr int T = 64, KS = 32;
   __shared__ double As[KS][T + 1];
   __shared__ double Bs[KS][T + 1];
   const int tid = threadIdx.x;
@@ -183,8 +189,10 @@ __global__ __launch_bounds__(256) void dgemm_kernel(SgemmArgs g, const TA* __res
   const int kz = g.ksplit ? (int)blockIdx.z : 0;
   const int b = g.ksplit ? 0 : (int)blockIdx.z, b1 = b / g.nb2, b2 = b - b1 * g.nb2;
   const int kbeg = kz * g.ksplit, kend = g.ksplit ? min(g.K, kbeg + g.ksplit) : g.K;
-  const TA* A = A0 + b1 * g.sa1 + b2 * g.sa2;
-  const TB* B = B0 + b1 * g.sb1 + b2 * g.sb2;
+  typedef TileLoad<AK, T, KS, TA> LA;
+  typedef TileLoad<BK, T, KS, TB> LB;
+  const LA la(A0 + b1 * g.sa1 + b2 * g.sa2, g.am, g.ak, g.M, m0);
+  const LB lb(B0 + b1 * g.sb1 + b2 * g.sb2, g.bn, g.bk, g.N, n0);
   const int lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
   const int li = lane & 15, lk = lane >> 4;
   f64x4 acc[2][2];
@@ -193,37 +201,26 @@ __global__ __launch_bounds__(256) void dgemm_kernel(SgemmArgs g, const TA* __res
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
   // the next k chunk's operands are loaded into registers while the current
-  // chunk's MFMAs run (consecutive threads walk each operand's contiguous
-  // dimension); they stay in their own type until the LDS store, so that a
-  // conversion does not wait for the loads in front of the MFMAs
-  TA ra[PER];
-  TB rb[PER];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int e = tid + 256 * u;
-      const int r = AK ? e / KS : e % T, k = AK ? e % KS : e / T;
-      const int gr = m0 + r, gk = k0 + k;
-      ra[u] = (gr < g.M && gk < kend) ? A[gr * g.am + gk * g.ak] : (TA)0;
-    }
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int e = tid + 256 * u;
-      const int r = BK ? e / KS : e % T, k = BK ? e % KS : e / T;
-      const int gr = n0 + r, gk = k0 + k;
-      rb[u] = (gr < g.N && gk < kend) ? B[gr * g.bn + gk * g.bk] : (TB)0;
-    }
-  };
-  load(kbeg);
+  // chunk's MFMAs run; they stay in their own type until the LDS store, so
+  // that a conversion does not wait for the loads in front of the MFMAs
+  typename LA::run_t ra[LA::RUNS];
+  typename LB::run_t rb[LB::RUNS];
+  la.load(kbeg, kend, ra);
+  lb.load(kbeg, kend, rb);
   for (int k0 = kbeg; k0 < kend; k0 += KS) {
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int e = tid + 256 * u;
-      As[AK ? e % KS : e / T][AK ? e / KS : e % T] = (double)ra[u];
-      Bs[BK ? e % KS : e / T][BK ? e / KS : e % T] = (double)rb[u];
-    }
+    for (int i = 0; i < LA::RUNS; ++i)
+#pragma unroll
+      for (int u = 0; u < LA::V; ++u) As[la.k(i) + (AK ? u : 0)][la.row(i) + (AK ? 0 : u)] = (double)ra[i][u];
+#pragma unroll
+    for (int i = 0; i < LB::RUNS; ++i)
+#pragma unroll
+      for (int u = 0; u < LB::V; ++u) Bs[lb.k(i) + (BK ? u : 0)][lb.row(i) + (BK ? 0 : u)] = (double)rb[i][u];
     __syncthreads();
-    if (k0 + KS < kend) load(k0 + KS);
+    if (k0 + KS < kend) {
+      la.load(k0 + KS, kend, ra);
+      lb.load(k0 + KS, kend, rb);
+    }
 #pragma unroll
     for (int k = 0; k < KS; k += 4) {
       double av[2], bv[2];

@@ -93,3 +93,13 @@ def test_fp64_refinement_tiles(d, N, t):
     """fp32 mode: candidate lists that fill 32-row (16-row at d = 256) tiles in part."""
     w = configs.shrink(configs.get_workload(1), head_dim=d, n_kv_heads=2)
     _layer_case(w, configs.MODE_FP32, N, t, f"cfg1 fp32 d={d} N={N} t={t}")
+
+
+@pytest.mark.parametrize("N,t", [(1201, 67), (1204, 68), (520, 130)])
+def test_backward_tiles(N, t):
+    """8 KV heads, 8 cross heads of width 128: key-side products on 128 x 128
+    tiles with a short last tile, attention-side operands with rows that are
+    (1204, 68) and are not (1201, 67) 16-byte aligned, 64 x 64 tiles (520)."""
+    from tests.test_gpu_backward import _grad_case
+    w = configs.shrink(configs.get_workload(1), n_kv_heads=8, n_cross_heads=8)
+    _grad_case(w, f"8 x 8 heads N={N} t={t}", N=N, t=t)
