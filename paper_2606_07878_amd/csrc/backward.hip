@@ -275,7 +275,7 @@ still_status run_backward(const still_config* cfg, const Dims& m, const BPlan& p
   auto W = [](const void* x) { return (const float*)x; };
 
   // ------------------------------------------------------------ forward
-  hipLaunchKernelGGL(positions_kernel, dim3(1), dim3(256), 0, st, positions, N, t, (double*)pq, (double*)nullptr);
+  hipLaunchKernelGGL(positions_kernel, dim3(1), dim3(1024), 0, st, positions, N, t, (double*)pq, (double*)nullptr);
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(inv_freq64_kernel, dim3((d / 2 + 255) / 256), dim3(256), 0, st, theta, d, (double*)invf_b);
   HIP_TRY(hipGetLastError());

@@ -132,6 +132,12 @@ __host__ __device__ __forceinline__ long xtile_off(long h, long f, long n, long 
           (n & 7));
 }
 
+// Fragment-tiled W (rows = output widths, contiguous input dimension d2):
+// [row / 32][col / 16][lane = row % 32 + 32 * ((col / 8) % 2)][col % 8]
+__host__ __device__ __forceinline__ long wtile_off(long row, long col, long d2) {
+  return (((row >> 5) * (d2 >> 4) + (col >> 4)) << 9) + (((row & 31) + (((col >> 3) & 1) << 5)) << 3) + (col & 7);
+}
+
 // Keys whose fp16-path logit lies within this many log2 units of their row's
 // maximum are candidates for the exact-logit refinement of cross-attention.
 constexpr float REFINE_MARGIN = 10.f;

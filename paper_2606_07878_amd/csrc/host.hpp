@@ -147,8 +147,7 @@ struct Dims {
 
 struct Plan {
   size_t pq, tab_ck, tab_cq, tab_bq;   // (cos, sin) tables of the latent positions (and, fp32 mode, of the keys)
-  size_t wconv;          // bf16 mode: the layer's weight matrices converted to fp16
-  size_t wkt;            // bf16 mode: fragment-tiled fp16 copy of the cross-attention W_K
+  size_t wconv;          // bf16 mode: the layer's weight matrices converted to fp16 (ca_wk fragment-tiled)
   size_t X, XT, Z, Y, q, partq, rq, O;
   size_t Ylo, qex, cval, cidx, cand, ocnt, ridx, rval, rcnt, rpart, crow, ccount;   // logit refinement
   size_t q64;                   // fp32 mode: fp64 queries of the refinement
@@ -337,7 +336,6 @@ inline Plan make_plan(const still_config* c, const Dims& m) {
   p.wconv = m.fp32 ? 0 : take(2ul * matrix_elems(c, m));
   p.kvpart = m.fp32 ? 0 : take(4ul * m.H * stage_blocks(m));
   p.hscale = m.fp32 ? 0 : take(4ul * 2 * m.H);
-  p.wkt = m.fp32 ? 0 : take(2ul * m.Ec * m.d2);
   p.X = take(cs * HN * m.d2);
   p.XT = take(cs * (size_t)m.H * m.d2 * m.Npad);
   p.Z = take(4ul * Ht * m.D);

@@ -28,27 +28,10 @@
 
 namespace still {
 
-// Fragment-tiled W (rows = output widths, contiguous input dimension d2):
-// [row / 32][col / 16][lane = row % 32 + 32 * ((col / 8) % 2)][col % 8]
-__host__ __device__ __forceinline__ long wtile_off(long row, long col, long d2) {
-  return (((row >> 5) * (d2 >> 4) + (col >> 4)) << 9) + (((row & 31) + (((col >> 3) & 1) << 5)) << 3) + (col & 7);
-}
-
 // Width held by position p (0..15) of a 16-width step in the permuted order.
 __host__ __device__ __forceinline__ int kperm_width(int p) {
   const int g = p >> 3, e = p & 7;
   return e < 4 ? 4 * g + e : 8 + 4 * g + (e - 4);
-}
-
-// W (fp16, row-major [rows][d2]) -> fragment-tiled copy; one thread per
-// 16-byte unit.
-static __global__ void tile_w_kernel(const f16* __restrict__ w, long rows, int d2, f16* __restrict__ out) {
-  const long units = rows * (d2 / 8);
-  for (long u = blockIdx.x * (long)blockDim.x + threadIdx.x; u < units; u += (long)gridDim.x * blockDim.x) {
-    const long row = u / (d2 / 8);
-    const int col = (int)(u - row * (d2 / 8)) * 8;
-    *(uint4*)(out + wtile_off(row, col, d2)) = *(const uint4*)(w + row * d2 + col);
-  }
 }
 
 struct KprojArgs {

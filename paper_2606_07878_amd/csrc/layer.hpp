@@ -174,6 +174,8 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
       segs.src[ns] = src;
       segs.dst[ns] = dst;
       segs.n8[ns] = n / 8;
+      for (const still_block_weights& cb : cblocks)   // the key projection reads W_K fragment-tiled
+        if (slot == &cb.ca_wk) segs.tile[ns] = m.d2;
       if (n / 8 > longest) longest = n / 8;
       *slot = dst;
       dst += rup(n, 128);
@@ -196,37 +198,41 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
     float* part = sizeof(CT) == 2 ? (float*)(ws + p.kvpart) : nullptr;
     float* hscale = sizeof(CT) == 2 ? (float*)(ws + p.hscale) : nullptr;
     hipLaunchKernelGGL((stage_x_kernel<IT, CT>), grid, dim3(256), lds, st, (const IT*)Kp, (const IT*)Vp, positions,
-                       invf_b, m.N, m.d, X, XT, m.Npad, RW, part, (const float*)hscale, 0);
+                       invf_b, m.N, m.d, X, XT, m.Npad, RW, part, hscale, 0);
     HIP_TRY(hipGetLastError());
     if (hscale) {
-      hipLaunchKernelGGL(kv_scale_kernel, dim3(m.H), dim3(256), 0, st, (const float*)part, (int)grid.x, m.H, hscale);
-      HIP_TRY(hipGetLastError());
+      const bool fold = grid.x <= 256;   // the scale formed inside the second pass
+      if (!fold) {
+        hipLaunchKernelGGL(kv_scale_kernel, dim3(m.H), dim3(256), 0, st, (const float*)part, (int)grid.x, m.H, hscale);
+        HIP_TRY(hipGetLastError());
+      }
       hipLaunchKernelGGL((stage_x_kernel<IT, CT>), grid, dim3(256), lds, st, (const IT*)Kp, (const IT*)Vp, positions,
-                         invf_b, m.N, m.d, X, XT, m.Npad, RW, (float*)nullptr, (const float*)hscale, 1);
+                         invf_b, m.N, m.d, X, XT, m.Npad, RW, fold ? part : (float*)nullptr, hscale, fold ? 2 : 1);
       HIP_TRY(hipGetLastError());
     }
   }
-  {
-    TIMED(STILL_K_OTHER);
-    hipLaunchKernelGGL((init_z_kernel<IT>), dim3(grid1d(Ht * m.D / 8)), dim3(256), 0, st, (const IT*)w->latents, Z, Ht * m.D);
-  }
-  HIP_TRY(hipGetLastError());
+  const IT* lat = (const IT*)w->latents;   // until the first norm has written them to Z
   auto rmsnorm = [&]() -> hipError_t {
     TIMED(STILL_K_OTHER);
-    hipLaunchKernelGGL((rmsnorm_kernel<CT>), dim3((unsigned)((Ht + 3) / 4)), dim3(256), 0, st, Z, Y, Ht, m.D,
-                       cfg->rms_eps);
+    hipLaunchKernelGGL((rmsnorm_kernel<CT, IT, false>), dim3((unsigned)((Ht + 3) / 4)), dim3(256), 0, st, Z, lat, Y,
+                       (CT*)nullptr, Ht, m.D, cfg->rms_eps);
+    lat = nullptr;
     return hipGetLastError();
   };
-  auto rmsnorm_split = [&](f16* hi, f16* lo) -> hipError_t {
+  auto rmsnorm_split = [&](CT* hi, CT* lo) -> hipError_t {
     TIMED(STILL_K_OTHER);
-    hipLaunchKernelGGL(rmsnorm_split_kernel, dim3((unsigned)((Ht + 3) / 4)), dim3(256), 0, st, Z, hi, lo, Ht, m.D,
-                       cfg->rms_eps);
+    hipLaunchKernelGGL((rmsnorm_kernel<CT, IT, true>), dim3((unsigned)((Ht + 3) / 4)), dim3(256), 0, st, Z, lat, hi, lo,
+                       Ht, m.D, cfg->rms_eps);
+    lat = nullptr;
     return hipGetLastError();
   };
-  auto finalize = [&](const float* part, long rows, int nh, int np, float* rn) -> hipError_t {
+  // the factors of nh heads' queries (rows_q rows, np_q partials) and keys
+  auto finalize = [&](int nh, const float* part_q, long rows_q, int np_q, float* rn_q, const float* part_k, long rows_k,
+                      int np_k, float* rn_k) -> hipError_t {
     TIMED(STILL_K_OTHER);
-    hipLaunchKernelGGL(finalize_norm_kernel, dim3(grid1d(rows * nh)), dim3(256), 0, st, part, rows, nh, np,
-                       cfg->l2_eps, rn);
+    const NormSegs segs = {{{part_q, rows_q, np_q, rn_q}, {part_k, rows_k, np_k, rn_k}}};
+    hipLaunchKernelGGL(finalize_norm_kernel, dim3(grid1d(std::max(rows_q, rows_k) * nh), 2), dim3(256), 0, st, segs, nh,
+                       cfg->l2_eps);
     return hipGetLastError();
   };
 
@@ -235,7 +241,7 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
     // ---------------- cross-attention: Z += CrossAttn(RMSNorm(Z), X)
     if (cfg->cross_every_block || b == 0) {
       if constexpr (sizeof(CT) == 2) {
-        if (m.R > 0 && !m.fp32) HIP_TRY(rmsnorm_split((f16*)Y, (f16*)(ws + p.Ylo)));
+        if (m.R > 0 && !m.fp32) HIP_TRY(rmsnorm_split(Y, (CT*)(ws + p.Ylo)));
         else HIP_TRY(rmsnorm());
       } else {
         HIP_TRY(rmsnorm());
@@ -260,13 +266,9 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
         // k = RoPE_c(k~), k~ = X W_K^T + b_K, fused kernel writing the tiled key
         // layout; one sum-of-squares partial per (row, cross head)
         TIMED(STILL_K_KPROJ);
-        f16* wkt = (f16*)(ws + p.wkt);
-        hipLaunchKernelGGL(tile_w_kernel, dim3(grid1d((long)m.Ec * m.d2 / 8)), dim3(256), 0, st,
-                           (const f16*)bw.ca_wk, (long)m.Ec, m.d2, wkt);
-        HIP_TRY(hipGetLastError());
         KprojArgs ka;
         ka.X = (const f16*)X;
-        ka.wkt = wkt;
+        ka.wkt = (const f16*)bw.ca_wk;   // fragment-tiled by the conversion
         ka.bias = bw.ca_bk;
         ka.pos = positions;
         ka.invf = invf_c;
@@ -301,7 +303,6 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
                              dim3(256), 0, st, (f16*)k, (long)m.H * m.nc, (int)m.N, (long)m.Npad, m.dc);
           HIP_TRY(hipGetLastError());
         }
-        HIP_TRY(finalize(partk, HN, m.nc, 1, rk));
       } else {  // k = RoPE_c(k~) with k~ = X W_K^T + b_K
         GemmArgs g = gargs((int)HN, m.Ec / 2, m.d2, X, m.d2, bw.ca_wk, m.d2, k, m.Ec);
         if (Tile<CT>::BM % m.H == 0) {   // tiles span the same keys of every KV head: shared table rows
@@ -315,9 +316,8 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
         g.part = partk;
         g.ldpart = HN;
         HIP_TRY((gemm<CT, CT, CT, CT, IT, EPI_PAIR>(g, 1, st, STILL_K_KPROJ)));
-        HIP_TRY(finalize(partk, HN, m.nc, m.np_c, rk));
       }
-      HIP_TRY(finalize(partq, Ht, m.nc, wide_c ? m.dc / 256 * 2 : m.np_c, rq));
+      HIP_TRY(finalize(m.nc, partq, Ht, wide_c ? m.dc / 256 * 2 : m.np_c, rq, partk, HN, sizeof(CT) == 2 ? 1 : m.np_c, rk));
       {
         AttnArgs a;
         a.q = q;
@@ -391,7 +391,7 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
               rk_.invf_b = invf_b;
               rk_.pos = positions;
               rk_.invf_c = invf_c;
-              rk_.wkt = (const f16*)(ws + p.wkt);
+              rk_.wkt = (const f16*)bw.ca_wk;
               rk_.bias = bw.ca_bk;
               rk_.ridx = ridx;
               rk_.crow = crow;
@@ -567,8 +567,8 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
             HIP_TRY(hipGetLastError());
           }
         }
-        HIP_TRY(finalize(partqs, Ht, m.ns, wide_s ? m.ds / 256 * 2 : m.np_s, rqs));
-        HIP_TRY(finalize(partks, Ht, m.ns, wide_s ? m.ds / 256 * 2 : m.np_s, rks));
+        const int nps = wide_s ? m.ds / 256 * 2 : m.np_s;
+        HIP_TRY(finalize(m.ns, partqs, Ht, nps, rqs, partks, Ht, nps, rks));
         AttnArgs a;
         memset(&a, 0, sizeof a);
         a.q = qs;
@@ -655,8 +655,8 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
           HIP_TRY(hipGetLastError());
         }
       }
-      HIP_TRY(finalize(partqs, Ht, m.ns, wide_s ? m.ds / 256 * 2 : m.np_s, rqs));
-      HIP_TRY(finalize(partks, Ht, m.ns, wide_s ? m.ds / 256 * 2 : m.np_s, rks));
+      const int nps = wide_s ? m.ds / 256 * 2 : m.np_s;
+      HIP_TRY(finalize(m.ns, partqs, Ht, nps, rqs, partks, Ht, nps, rks));
       {  // S = s * q k^T with the QK-norm factors, per (h, c)
         GemmArgs g = gargs(m.t, m.t, m.ds, qs, m.Es, ks, m.Es, Ssa, m.tpad);
         g.nb2 = m.ns;

@@ -9,54 +9,88 @@ namespace still {
 
 // ---------------------------------------------------------------------------
 // Latent / output positions: p_i = p_min + i (p_max - p_min)/(t-1) over the
-// supplied key positions (p_0 = p_min when t = 1).  One workgroup.
+// supplied key positions (p_0 = p_min when t = 1).  One workgroup, bound by the
+// latency of its loads: 16 waves with four loads each in flight.
 // ---------------------------------------------------------------------------
-static __global__ __launch_bounds__(256) void positions_kernel(const double* __restrict__ p, long N, int t,
-                                                        double* __restrict__ pq, double* __restrict__ out) {
-  __shared__ double smin[256], smax[256];
-  double lo = INFINITY, hi = -INFINITY;
-  for (long i = threadIdx.x; i < N; i += 256) {
-    const double v = p[i];
-    lo = fmin(lo, v);
-    hi = fmax(hi, v);
+static __global__ __launch_bounds__(1024) void positions_kernel(const double* __restrict__ p, long N, int t,
+                                                         double* __restrict__ pq, double* __restrict__ out) {
+  __shared__ double smin[16], smax[16];
+  double lo[4], hi[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    lo[u] = INFINITY;
+    hi[u] = -INFINITY;
   }
-  smin[threadIdx.x] = lo;
-  smax[threadIdx.x] = hi;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      smin[threadIdx.x] = fmin(smin[threadIdx.x], smin[threadIdx.x + s]);
-      smax[threadIdx.x] = fmax(smax[threadIdx.x], smax[threadIdx.x + s]);
+  for (long i0 = threadIdx.x; i0 < N; i0 += 4096) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = p[min(i0 + 1024 * u, N - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      lo[u] = fmin(lo[u], v[u]);
+      hi[u] = fmax(hi[u], v[u]);
     }
-    __syncthreads();
   }
-  lo = smin[0];
-  hi = smax[0];
-  const double step = t > 1 ? (hi - lo) / (double)(t - 1) : 0.0;
-  for (int i = threadIdx.x; i < t; i += 256) {
-    const double v = lo + (double)i * step;
+  double l = fmin(fmin(lo[0], lo[1]), fmin(lo[2], lo[3])), h = fmax(fmax(hi[0], hi[1]), fmax(hi[2], hi[3]));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    l = fmin(l, __shfl_xor(l, o));
+    h = fmax(h, __shfl_xor(h, o));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    smin[threadIdx.x >> 6] = l;
+    smax[threadIdx.x >> 6] = h;
+  }
+  __syncthreads();
+  l = smin[0];
+  h = smax[0];
+#pragma unroll
+  for (int w = 1; w < 16; ++w) {
+    l = fmin(l, smin[w]);
+    h = fmax(h, smax[w]);
+  }
+  const double step = t > 1 ? (h - l) / (double)(t - 1) : 0.0;
+  for (int i = threadIdx.x; i < t; i += 1024) {
+    const double v = l + (double)i * step;
     pq[i] = v;
     if (out) out[i] = v;
   }
 }
 
 // ---------------------------------------------------------------------------
-// Rotation table: tab[r][j] = (cos, sin)(p_r * base^(-2j/w)), j < w/2.
-// Angles are formed and reduced in float64 (positions up to ~1e5 times
-// frequencies near 1 need more than float32's 24 bits), then rounded.
+// A call's tables in one launch, one per grid row (tens of thousands of
+// entries: a launch each costs more than its work).  Rotation tables:
+// tab[r][j] = (cos, sin)(p_r * base^(-2j/w)), j < w/2, angles formed and
+// reduced in float64 (positions up to ~1e5 times frequencies near 1 need more
+// than float32's 24 bits), then rounded.  Without `tab`: the frequencies
+// base^(-2j/w) themselves, fp64, into inv.
 // ---------------------------------------------------------------------------
-static __global__ void rope_table_kernel(const double* __restrict__ pos, long R, int w, double base,
-                                  float2* __restrict__ tab) {
-  const int hh = w / 2;
-  const long total = R * hh;
+constexpr int TABLE_SEGS = 5;
+struct TableSegs {
+  struct Seg {
+    const double* pos;
+    long R;
+    int w;
+    double base;
+    float2* tab;
+    double* inv;
+  } seg[TABLE_SEGS];
+};
+static __global__ void tables_kernel(TableSegs ts) {
+  const TableSegs::Seg s = ts.seg[blockIdx.y];
+  const int hh = s.w / 2;
+  const long total = s.tab ? s.R * hh : hh;
   for (long idx = blockIdx.x * (long)blockDim.x + threadIdx.x; idx < total; idx += (long)gridDim.x * blockDim.x) {
     const long r = idx / hh;
     const int j = (int)(idx - r * hh);
-    const double inv = pow(base, -2.0 * (double)j / (double)w);
-    const double ang = pos[r] * inv;
+    const double inv = pow(s.base, -2.0 * (double)j / (double)s.w);
+    if (!s.tab) {
+      s.inv[j] = inv;
+      continue;
+    }
     double sn, cs;
-    sincos(ang, &sn, &cs);
-    tab[idx] = make_float2((float)cs, (float)sn);
+    sincos(s.pos[r] * inv, &sn, &cs);
+    s.tab[idx] = make_float2((float)cs, (float)sn);
   }
 }
 
@@ -109,43 +143,61 @@ template <class T> __device__ __forceinline__ void store8(T* p, const float (&v)
 // ---------------------------------------------------------------------------
 // scale[h] = 2^-e_h and scale[H + h] = 2^e_h from the per-workgroup maxima
 // of |K|, |V| that the staging pass wrote for head h.  One workgroup per head.
-static __global__ __launch_bounds__(256) void kv_scale_kernel(const float* __restrict__ part, int nblk, int H,
-                                                       float* __restrict__ scale) {
-  __shared__ float red[4];
-  const int h = blockIdx.x;
+static __device__ __forceinline__ void kv_scale_of(float mx, float& s, float& inv) {
+  s = inv = 1.f;
+  while (mx * s > 16384.f) {   // at most ~113 halvings (mx < 2^128; NaN stops at once)
+    s *= 0.5f;
+    inv *= 2.f;
+  }
+}
+// the largest of a head's nblk maxima, for every thread of a 256-thread workgroup
+static __device__ __forceinline__ float kv_head_max(const float* __restrict__ part, int nblk, float (&red)[4]) {
   float m = 0.f;
-  for (int b = threadIdx.x; b < nblk; b += 256) m = fmaxf(m, part[(long)h * nblk + b]);
+  for (int b = threadIdx.x; b < nblk; b += 256) m = fmaxf(m, part[b]);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    float s = 1.f, inv = 1.f;
-    while (m * s > 16384.f) {   // at most ~113 halvings (m < 2^128; NaN stops at once)
-      s *= 0.5f;
-      inv *= 2.f;
-    }
-    scale[h] = s;
-    scale[H + h] = inv;
-  }
+  return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+}
+static __global__ __launch_bounds__(256) void kv_scale_kernel(const float* __restrict__ part, int nblk, int H,
+                                                       float* __restrict__ scale) {
+  __shared__ float red[4];
+  const int h = blockIdx.x;
+  const float m = kv_head_max(part + (long)h * nblk, nblk, red);
+  if (threadIdx.x == 0) kv_scale_of(m, scale[h], scale[H + h]);
 }
 
 // Staging passes: pass 0 stages every head unscaled and, with `part`,
 // writes each workgroup's max(|K|, |V|) (part[h][blockIdx.x]); pass 1
 // re-stages, times hscale[h], only the heads whose scale is not 1 (the
-// workgroups of the other heads exit at once).
+// workgroups of the other heads exit at once); pass 2 is pass 1 with the
+// scale formed from part by every workgroup and written to hscale by the
+// first: up to 256 workgroups per head (one load per thread) that costs less
+// than the launch of kv_scale_kernel.
 template <class IT, class CT>
 __global__ __launch_bounds__(256) void stage_x_kernel(const IT* __restrict__ K, const IT* __restrict__ V,
                                                       const double* __restrict__ pos, const double* __restrict__ invf,
                                                       long N, int d,
                                                       CT* __restrict__ X, CT* __restrict__ XT, long ldxt,
-                                                      int RW, float* __restrict__ part, const float* __restrict__ hscale,
+                                                      int RW, float* part, float* hscale,
                                                       int pass) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   CT* tile = (CT*)smem_raw;              // [RW][2d + 8]
   const int h = blockIdx.y;
-  const float sc = pass ? hscale[h] : 1.f;   // fp16 range scale of this head (exact power of two)
+  __shared__ float red[4];
+  float sc = 1.f;   // fp16 range scale of this head (exact power of two)
+  if (pass == 1) {
+    sc = hscale[h];
+  } else if (pass == 2) {
+    float inv;
+    kv_scale_of(kv_head_max(part + (long)h * gridDim.x, gridDim.x, red), sc, inv);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      hscale[h] = sc;
+      hscale[gridDim.y + h] = inv;
+    }
+    part = nullptr;
+  }
   if (sc == 1.f && pass) return;             // uniform
   float amax = 0.f;
   const long n0 = (long)blockIdx.x * RW;
@@ -209,7 +261,6 @@ __global__ __launch_bounds__(256) void stage_x_kernel(const IT* __restrict__ K, 
   if (part) {   // this workgroup's max |K|, |V| (reduced through the LDS tile's tail before phase 2 reuses nothing)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
-    __shared__ float red[4];
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = amax;
     __syncthreads();
     if (threadIdx.x == 0) part[(long)h * gridDim.x + blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
@@ -230,83 +281,62 @@ __global__ __launch_bounds__(256) void stage_x_kernel(const IT* __restrict__ K, 
   }
 }
 
-// Z = latents (fp32 residual stream).
-template <class IT>
-__global__ void init_z_kernel(const IT* __restrict__ lat, float* __restrict__ Z, long n) {
-  const long stride = (long)gridDim.x * blockDim.x, i0 = blockIdx.x * (long)blockDim.x + threadIdx.x;
-  if ((n & 7) == 0 && (((uintptr_t)lat | (uintptr_t)Z) & 15) == 0) {   // 8 values per thread and step
-    for (long i = i0; i < n / 8; i += stride) {
-      float v[8];
-      if constexpr (sizeof(IT) == 2) {
-        const uint4 u = *(const uint4*)(lat + 8 * i);
-        const uint32_t wd[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          v[2 * k] = to_f32(__builtin_bit_cast(IT, (uint16_t)(wd[k] & 0xffffu)));
-          v[2 * k + 1] = to_f32(__builtin_bit_cast(IT, (uint16_t)(wd[k] >> 16)));
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = to_f32(lat[8 * i + k]);
-      }
-      *(f32x4*)(Z + 8 * i) = f32x4{v[0], v[1], v[2], v[3]};
-      *(f32x4*)(Z + 8 * i + 4) = f32x4{v[4], v[5], v[6], v[7]};
+// Y = RMSNorm(Z) per row (non-parametric), one wave per row.  SPLIT: into a
+// high and a low fp16 part (Y ~= hi + lo to about 22 bits) for products whose
+// result must be more accurate than one fp16 rounding of Y allows.  With `lat`
+// (the first norm of a layer) the rows are read from the latent bank and also
+// written to Z, the fp32 residual stream they start.
+template <class OT, class IT, bool SPLIT>
+__global__ __launch_bounds__(256) void rmsnorm_kernel(float* __restrict__ Z, const IT* __restrict__ lat,
+                                                      OT* __restrict__ Y, OT* __restrict__ Ylo, long rows, int D,
+                                                      float eps) {
+  const long row = blockIdx.x * 4L + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (row >= rows) return;
+  float* z = Z + row * D;
+  float s = 0.f;
+  if (lat) {
+    const IT* l = lat + row * D;
+    for (int i = lane; i < D; i += 64) {
+      const float v = to_f32(l[i]);
+      z[i] = v;
+      s += v * v;
     }
   } else {
-    for (long i = i0; i < n; i += stride) Z[i] = to_f32(lat[i]);
+    for (int i = lane; i < D; i += 64) s += z[i] * z[i];
   }
-}
-
-// Y = RMSNorm(Z) per row (non-parametric), one wave per row.
-template <class OT>
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ Z, OT* __restrict__ Y, long rows,
-                                                      int D, float eps) {
-  const long row = blockIdx.x * 4L + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= rows) return;
-  const float* z = Z + row * D;
-  float s = 0.f;
-  for (int i = lane; i < D; i += 64) s += z[i] * z[i];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-  const float r = 1.f / sqrtf(s / (float)D + eps);
-  for (int i = lane; i < D; i += 64) Y[row * D + i] = from_f32<OT>(z[i] * r);
-}
-
-// Y = RMSNorm(Z) split into a high and a low fp16 part (Y ~= hi + lo to
-// about 22 bits) for products whose result must be more accurate than one
-// fp16 rounding of Y allows.
-static __global__ __launch_bounds__(256) void rmsnorm_split_kernel(const float* __restrict__ Z, f16* __restrict__ Yhi,
-                                                            f16* __restrict__ Ylo, long rows, int D, float eps) {
-  const long row = blockIdx.x * 4L + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= rows) return;
-  const float* z = Z + row * D;
-  float s = 0.f;
-  for (int i = lane; i < D; i += 64) s += z[i] * z[i];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
   const float r = 1.f / sqrtf(s / (float)D + eps);
   for (int i = lane; i < D; i += 64) {
-    const float y = z[i] * r;
-    const f16 hi = (f16)y;
-    Yhi[row * D + i] = hi;
-    Ylo[row * D + i] = (f16)(y - (float)hi);
+    const float y = (lat ? to_f32(lat[row * D + i]) : z[i]) * r;
+    const OT hi = from_f32<OT>(y);
+    Y[row * D + i] = hi;
+    if constexpr (SPLIT) Ylo[row * D + i] = from_f32<OT>(y - to_f32(hi));
   }
 }
 
 
 // rn[r][c] = 1 / max(sqrt(sum_p part[c*np + p][r]), eps)   (QK-norm factors)
-static __global__ void finalize_norm_kernel(const float* __restrict__ part, long rows, int nh, int np,
-                                     float eps, float* __restrict__ rn) {
-  const long total = rows * nh;
+// for the query and the key side at once (one grid row each)
+struct NormSegs {
+  struct Seg {
+    const float* part;
+    long rows;
+    int np;
+    float* rn;
+  } seg[2];
+};
+static __global__ void finalize_norm_kernel(NormSegs ns, int nh, float eps) {
+  const NormSegs::Seg s = ns.seg[blockIdx.y];
+  const long total = s.rows * nh;
   for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < total; i += (long)gridDim.x * blockDim.x) {
     const long r = i / nh;
     const int c = (int)(i - r * nh);
-    const float* p = part + (long)c * np * rows + r;   // partials [c*np + k][rows]
-    float s = 0.f;
-    for (int k = 0; k < np; ++k) s += p[(long)k * rows];
-    rn[i] = 1.f / fmaxf(sqrtf(s), eps);
+    const float* p = s.part + (long)c * s.np * s.rows + r;   // partials [c*np + k][rows]
+    float q = 0.f;
+    for (int k = 0; k < s.np; ++k) q += p[(long)k * s.rows];
+    s.rn[i] = 1.f / fmaxf(sqrtf(q), eps);
   }
 }
 
@@ -762,11 +792,14 @@ static __global__ void zero_ktile_tail_kernel(f16* __restrict__ k, long heads, i
 // Element-type conversion of up to CONV_SEGS weight matrices per launch
 // (bf16 -> fp16 for the MFMA operands), one segment per grid row, 8 elements
 // per thread and step; segment lengths are multiples of 8 and 16-byte aligned.
+// A segment with tile > 0 is a matrix of that many columns written
+// fragment-tiled (wtile_off).
 constexpr int CONV_SEGS = 16;
 struct ConvSegs {
   const void* src[CONV_SEGS];
   void* dst[CONV_SEGS];
   long n8[CONV_SEGS];   // length / 8
+  int tile[CONV_SEGS];
 };
 
 template <class IT, class CT>
@@ -775,8 +808,12 @@ __global__ void convert_kernel(ConvSegs segs) {
   const IT* src = (const IT*)segs.src[s];
   CT* dst = (CT*)segs.dst[s];
   const long n8 = segs.n8[s];
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n8; i += (long)gridDim.x * blockDim.x)
-    *(typename Mma<CT>::frag*)(dst + 8 * i) = VecLoad<CT, IT>::load(src + 8 * i);
+  const int tile8 = segs.tile[s] / 8;
+  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n8; i += (long)gridDim.x * blockDim.x) {
+    const long row = tile8 ? i / tile8 : 0;
+    const long at = tile8 ? wtile_off(row, 8 * (i - row * tile8), 8 * tile8) : 8 * i;
+    *(typename Mma<CT>::frag*)(dst + at) = VecLoad<CT, IT>::load(src + 8 * i);
+  }
 }
 
 }  // namespace still

@@ -16,21 +16,22 @@ static still_status prepare_tables(const Dims& m, const Plan& p, char* ws, const
                                    hipStream_t st) {
   double* pq = (double*)(ws + p.pq);
   TIMED(STILL_K_OTHER);
-  hipLaunchKernelGGL(positions_kernel, dim3(1), dim3(256), 0, st, positions, m.N, m.t, pq, out_positions);
+  hipLaunchKernelGGL(positions_kernel, dim3(1), dim3(1024), 0, st, positions, m.N, m.t, pq, out_positions);
   HIP_TRY(hipGetLastError());
-  auto table = [&](const double* pos, long R, int w, double base, size_t off) -> hipError_t {
-    hipLaunchKernelGGL(rope_table_kernel, dim3(grid1d(R * (w / 2))), dim3(256), 0, st, pos, R, w, base,
-                       (float2*)(ws + off));
-    return hipGetLastError();
+  TableSegs ts;
+  memset(&ts, 0, sizeof ts);
+  int n = 0;
+  long longest = 0;
+  auto table = [&](const double* pos, long R, int w, double base, float2* tab, double* inv) {
+    ts.seg[n++] = {pos, R, w, base, tab, inv};
+    longest = std::max(longest, (tab ? R : 1) * (w / 2));
   };
-  if (m.fp32) HIP_TRY(table(positions, m.N, m.dc, cbase, p.tab_ck));
-  hipLaunchKernelGGL(inv_freq64_kernel, dim3((m.dc / 2 + 255) / 256), dim3(256), 0, st, cbase, m.dc,
-                     (double*)(ws + p.invf_c));
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(table(pq, m.t, m.dc, cbase, p.tab_cq));
-  if (rerotate) HIP_TRY(table(pq, m.t, m.d, rope_theta, p.tab_bq));
-  hipLaunchKernelGGL(inv_freq64_kernel, dim3((m.d / 2 + 255) / 256), dim3(256), 0, st, rope_theta, m.d,
-                     (double*)(ws + p.invf_b));
+  if (m.fp32) table(positions, m.N, m.dc, cbase, (float2*)(ws + p.tab_ck), nullptr);
+  table(pq, m.t, m.dc, cbase, (float2*)(ws + p.tab_cq), nullptr);
+  if (rerotate) table(pq, m.t, m.d, rope_theta, (float2*)(ws + p.tab_bq), nullptr);
+  table(nullptr, 1, m.dc, cbase, nullptr, (double*)(ws + p.invf_c));
+  table(nullptr, 1, m.d, rope_theta, nullptr, (double*)(ws + p.invf_b));
+  hipLaunchKernelGGL(tables_kernel, dim3(grid1d(longest), n), dim3(256), 0, st, ts);
   HIP_TRY(hipGetLastError());
   return STILL_OK;
 }
