@@ -336,7 +336,8 @@ namespace still {
 // TFLOP/s); 9216 keys of width 2048 (D2 = 512): 4.32 ms with 64-latent tiles,
 // 3.20 now (966).  Listing the candidates costs 0.12 ms of the 1.50; with every
 // operand in the CU's L1 it would run at 1.24 PFLOP/s.
-//   D2 = 256: 128 latents x 512 keys (KT = 4);  D2 = 512: 128 x 256 (KT = 2).
+//   D2 = 256: 128 latents x 512 keys (KT = 4);  D2 = 512: 128 x 256 (KT = 2);
+//   up to 64 latents in all: 64 x 512.
 //   QK: S^T[key][lat] over the head width, in chunks of QC = 64 (one barrier
 //       per chunk).  Q chunks are copied straight from global memory into a
 //       ring of four LDS stages (direct loads, issued three chunks ahead of

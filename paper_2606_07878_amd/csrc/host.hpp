@@ -110,9 +110,13 @@ constexpr int GEMM_BN = 128;   // column tile of every GEMM (two halves of 64 pa
 constexpr int ATT_TT = 128;    // latents per attention workgroup
 constexpr int ATT_NB = 64;     // keys per attention block
 constexpr int ATT_TOPK = 4;    // keys tracked per latent half-lane for logit refinement (fp32 kernel)
-// keys per block of the fp16 attention kernel for a value width d2 (attn.hpp:
-// the logit and output accumulators share the registers)
-constexpr int xatt_kb(int d2) { return d2 == 256 ? 512 : 256; }
+// latents per workgroup of the fp16 attention kernel: half a tile of padding
+// costs more than the narrower tile's operand traffic (65536 keys, 64 latents,
+// 8 x 8 heads of width 1024, whole layer: 5.93 ms at 128, 5.54 at 64)
+constexpr int xatt_tt(int t) { return t <= 64 ? 64 : 128; }
+// ... and its keys per block for a value width d2 (attn.hpp: the logit and
+// output accumulators share the registers)
+constexpr int xatt_kb(int tt, int d2) { return d2 == 256 || (d2 == 512 && tt == 64) ? 512 : 256; }
 // keys per latent whose logits are recomputed accurately: every candidate
 // within the refinement margin, up to this many
 constexpr int REFINE_R = 256;
@@ -161,7 +165,7 @@ struct Plan {
   size_t total;
 };
 
-inline int key_block(const Dims& m) { return m.fp32 ? ATT_NB : xatt_kb(m.d2); }
+inline int key_block(const Dims& m) { return m.fp32 ? ATT_NB : xatt_kb(m.att_tt, m.d2); }
 
 // Key splits of the fp16 attention kernel (one workgroup per CU): the
 // workgroups run in rounds of 256, so the time is about rounds x (key blocks
@@ -243,7 +247,7 @@ inline still_status make_dims(const still_config* c, int64_t N, int32_t t, Dims*
   m->ncand_fixed = 2 * ATT_TOPK;
   m->ncand = m->ncand_fixed + ATT_OVF;
   m->R = REFINE_R;
-  m->att_tt = 128;
+  m->att_tt = m->fp32 ? 128 : xatt_tt(t);
   m->splits = choose_splits(*m);
   m->keys_per_split = rup((m->N + m->splits - 1) / m->splits, key_block(*m));
   m->splits = (int)((m->N + m->keys_per_split - 1) / m->keys_per_split);
@@ -253,8 +257,8 @@ inline still_status make_dims(const still_config* c, int64_t N, int32_t t, Dims*
   m->sa_splits = 1;
   m->sa_kps = m->tpadk;
   if (m->sa_flash) {
-    const int kb = xatt_kb(m->ds);
-    const long wgs = (long)((t + 127) / 128) * m->H * m->ns;
+    const int tt = xatt_tt(t), kb = xatt_kb(tt, m->ds);
+    const long wgs = (long)((t + tt - 1) / tt) * m->H * m->ns;
     const long sp = balanced_splits(wgs, (t + kb - 1) / kb, kb);
     m->sa_kps = rup((t + sp - 1) / sp, kb);
     m->sa_splits = (int)((t + m->sa_kps - 1) / m->sa_kps);

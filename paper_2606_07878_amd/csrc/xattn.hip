@@ -5,20 +5,26 @@
 
 namespace still {
 
-template <int D2>
+template <int TT, int D2>
 static void launch(const AttnArgs& a, bool track, dim3 grid, hipStream_t st) {
-  constexpr int KT = xatt_kb(D2) / 128;
+  constexpr int KT = xatt_kb(TT, D2) / 128;
   if (track)
-    hipLaunchKernelGGL((xattn_f16_kernel<ATT_TT, D2, true, KT>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((xattn_f16_kernel<TT, D2, true, KT>), grid, dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((xattn_f16_kernel<ATT_TT, D2, false, KT>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((xattn_f16_kernel<TT, D2, false, KT>), grid, dim3(256), 0, st, a);
+}
+
+template <int TT>
+static void launch(const AttnArgs& a, bool track, int splits, hipStream_t st) {
+  const dim3 grid((unsigned)((a.t + TT - 1) / TT * a.H * a.nc * splits));
+  if (a.d2 == 128) launch<TT, 128>(a, track, grid, st);
+  else if (a.d2 == 256) launch<TT, 256>(a, track, grid, st);
+  else launch<TT, 512>(a, track, grid, st);
 }
 
 hipError_t launch_xattn_f16(const AttnArgs& a, bool track, int splits, hipStream_t st) {
-  const dim3 grid((unsigned)((a.t + ATT_TT - 1) / ATT_TT * a.H * a.nc * splits));
-  if (a.d2 == 128) launch<128>(a, track, grid, st);
-  else if (a.d2 == 256) launch<256>(a, track, grid, st);
-  else launch<512>(a, track, grid, st);
+  if (xatt_tt(a.t) == 64) launch<64>(a, track, splits, st);
+  else launch<128>(a, track, splits, st);
   return hipGetLastError();
 }
 
