@@ -137,6 +137,7 @@ struct Dims {
   int ncand_fixed;      // ... of which the fixed lists (then up to ATT_OVF overflow entries)
   int att_tt;           // latents per attention workgroup
   int splits;           // split-N factor of the cross-attention
+  int max_splits;       // ... for which the workspace is sized
   long keys_per_split;
   // latent self-attention on the fp16 flash kernel (bf16 mode, d_s of 128,
   // 256 or 512): keys and values in its tiled layouts with tpadk keys per
@@ -171,11 +172,17 @@ inline int key_block(const Dims& m) { return m.fp32 ? ATT_NB : xatt_kb(m.att_tt,
 // workgroups run in rounds of 256, so the time is about rounds x (key blocks
 // per split + the start and end of a workgroup, about half a block of 256
 // keys); the fewest splits within 2 % of the best.
+// The workspace is sized for splits_cap, which unlike the choice does not fall
+// with fewer keys: a buffer sized for a range of keys serves every shorter one.
+inline long splits_cap(long wgs, long nblocks) {
+  const long s = (512 + wgs - 1) / wgs;   // two workgroups per CU; twice that where one split leaves CUs idle
+  return std::max(1l, std::min(nblocks, wgs >= 256 ? s : 2 * s));
+}
 inline int balanced_splits(long wgs, long nblocks, int kb) {
   const double fixed = 128.0 / kb;
   double best = 0;
   long pick = 1;
-  for (long want = 1; want <= nblocks; ++want) {
+  for (long want = 1; want <= splits_cap(wgs, nblocks); ++want) {
     const long per = (nblocks + want - 1) / want, s = (nblocks + per - 1) / per;
     if (s != want) continue;   // the same blocks per split with fewer splits was looked at already
     const double cost = (double)((wgs * s + 255) / 256) * ((double)per + fixed);
@@ -183,19 +190,20 @@ inline int balanced_splits(long wgs, long nblocks, int kb) {
       best = cost;
       pick = s;
     }
-    if (wgs * s >= 8 * 256) break;
   }
   return (int)pick;
 }
 
-inline int choose_splits(const Dims& m) {
-  const long wgs = (long)((m.t + m.att_tt - 1) / m.att_tt) * m.H * m.nc;
-  const long nblocks = (m.N + key_block(m) - 1) / key_block(m);
-  if (!m.fp32) return balanced_splits(wgs, nblocks, key_block(m));
-  long s = (1024 + wgs - 1) / wgs;   // fp32 kernel: at least 4 workgroups per CU
-  if (s > nblocks) s = nblocks;
-  if (s < 1) s = 1;
-  return (int)s;
+inline void choose_splits(Dims* m) {
+  const long wgs = (long)((m->t + m->att_tt - 1) / m->att_tt) * m->H * m->nc;
+  const long nblocks = (m->N + key_block(*m) - 1) / key_block(*m);
+  if (m->fp32) {
+    m->max_splits = (int)std::max(1l, std::min(nblocks, (1024 + wgs - 1) / wgs));   // at least 4 workgroups per CU
+    m->splits = m->max_splits;
+  } else {
+    m->max_splits = (int)splits_cap(wgs, nblocks);
+    m->splits = balanced_splits(wgs, nblocks, key_block(*m));
+  }
 }
 
 inline still_status make_dims(const still_config* c, int64_t N, int32_t t, Dims* m) {
@@ -248,7 +256,7 @@ inline still_status make_dims(const still_config* c, int64_t N, int32_t t, Dims*
   m->ncand = m->ncand_fixed + ATT_OVF;
   m->R = REFINE_R;
   m->att_tt = m->fp32 ? 128 : xatt_tt(t);
-  m->splits = choose_splits(*m);
+  choose_splits(m);
   m->keys_per_split = rup((m->N + m->splits - 1) / m->splits, key_block(*m));
   m->splits = (int)((m->N + m->keys_per_split - 1) / m->keys_per_split);
   m->tpadk = (int)rup(t, 256);
@@ -405,6 +413,12 @@ inline Plan make_plan(const still_config* c, const Dims& m) {
   p.hid = take(cs * Ht * (m.F > 0 ? m.F : 1));
   p.total = (off > end1 ? off : end1) + 256;
   return p;
+}
+
+// bytes of workspace a call must be given
+inline size_t workspace_total(const still_config* c, Dims m) {
+  m.splits = m.max_splits;
+  return make_plan(c, m).total;
 }
 
 inline int grid1d(long n, int per = 256) {

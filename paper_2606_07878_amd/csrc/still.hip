@@ -72,8 +72,9 @@ static still_status compact(const still_config* cfg, int32_t L, const still_laye
   }
   const Plan p = make_plan(cfg, m);
   if (!workspace) return fail(STILL_E_WORKSPACE, "workspace is NULL");
-  if (workspace_bytes < p.total)
-    return fail(STILL_E_WORKSPACE, "workspace of %zu bytes, need %zu", workspace_bytes, p.total);
+  const size_t need = workspace_total(cfg, m);
+  if (workspace_bytes < need)
+    return fail(STILL_E_WORKSPACE, "workspace of %zu bytes, need %zu", workspace_bytes, need);
   char* ws = (char*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
   hipStream_t st = (hipStream_t)stream;
   (void)hipGetLastError();  // clear a stale error so launch checks report this call
@@ -106,7 +107,8 @@ static still_status compact(const still_config* cfg, int32_t L, const still_laye
 // ---------------------------------------------------------------------------
 struct AttendPlan {
   int R, splits, cps, kc;
-  size_t opart, mpart, lpart, total;
+  size_t opart, mpart, lpart, need;   // offsets of the call's partials, bytes it uses
+  size_t total;                       // bytes still_attend_workspace_size reports (>= need)
 };
 
 constexpr int ATTEND_TARGET_BLOCKS = 2048;   // one-wave blocks per launch that keep the chip streaming
@@ -142,11 +144,23 @@ static still_status attend_plan(const still_attend_config* c, AttendPlan* ap) {
   ap->R = c->group * c->n_queries;
   ap->cps = (int)std::min(rup((chunks + per_head - 1) / per_head, unit), chunks);
   ap->splits = (int)((chunks + ap->cps - 1) / ap->cps);
-  const size_t slots = (size_t)ap->splits * c->n_kv_heads * ap->R;
-  ap->opart = 0;
-  ap->mpart = rup((long)(slots * c->head_dim * sizeof(float)), 256);
-  ap->lpart = ap->mpart + rup((long)(slots * sizeof(float)), 256);
-  ap->total = ap->lpart + rup((long)(slots * sizeof(float)), 256) + 256;   // + alignment slack
+  auto bytes = [&](long splits, AttendPlan* at) -> size_t {
+    const size_t slots = (size_t)splits * c->n_kv_heads * ap->R;
+    at->opart = 0;
+    at->mpart = rup((long)(slots * c->head_dim * sizeof(float)), 256);
+    at->lpart = at->mpart + rup((long)(slots * sizeof(float)), 256);
+    return at->lpart + rup((long)(slots * sizeof(float)), 256) + 256;   // + alignment slack
+  };
+  ap->need = bytes(ap->splits, ap);
+  // The size reported is that of one-wave splits at every row count, which a
+  // buffer sized for a longer context then has for a shorter one: the matrix
+  // kernel's splits are at least four times as long, so a longer call can need
+  // less than a shorter call on the decode kernel.
+  AttendPlan fine;
+  const int kf = R <= 8 ? (R <= 4 ? 8 : 4) * (64 / (c->head_dim * esize / 16)) : 64;
+  const long cf = ((long)c->t + kf - 1) / kf + ((long)c->n_suffix + kf - 1) / kf;
+  const long pf = std::max(1L, (long)ATTEND_TARGET_BLOCKS / c->n_kv_heads), sf = (cf + pf - 1) / pf;
+  ap->total = std::max(ap->need, bytes((cf + sf - 1) / sf, &fine));
   return STILL_OK;
 }
 
@@ -207,7 +221,7 @@ extern "C" {
 size_t still_workspace_size(const still_config* cfg, int64_t N, int32_t t, int32_t n_layers) {
   Dims m;
   if (n_layers < 1 || make_dims(cfg, N, t, &m) != STILL_OK) return 0;
-  return make_plan(cfg, m).total;
+  return workspace_total(cfg, m);
 }
 
 still_status still_compact_layer(const still_config* cfg, const still_layer_weights* w, const void* K, const void* V,
@@ -265,8 +279,8 @@ still_status still_attend(const still_attend_config* cfg, const void* q, const d
   if (cfg->rope_theta > 0.0 && (!q_positions || ((uintptr_t)q_positions & 7u)))
     return fail(STILL_E_INVAL, "rope_theta > 0 needs 8-byte aligned q_positions");
   if (!workspace) return fail(STILL_E_WORKSPACE, "workspace is NULL");
-  if (workspace_bytes < ap.total)
-    return fail(STILL_E_WORKSPACE, "workspace of %zu bytes, need %zu", workspace_bytes, ap.total);
+  if (workspace_bytes < ap.need)
+    return fail(STILL_E_WORKSPACE, "workspace of %zu bytes, need %zu", workspace_bytes, ap.need);
   char* ws = (char*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
   ConsumerArgs a;
   a.q = q;
