@@ -77,7 +77,8 @@ typedef enum {
 
 /* Shapes the kernels take (anything else the paper allows returns
  * STILL_E_UNSUPPORTED): head_dim 64, 128 or 256; cross- and self-attention
- * head widths multiples of 128; latent_dim and ffn_hidden multiples of 8;
+ * head widths multiples of 128 (cross widths below 2^24); latent_dim and
+ * ffn_hidden multiples of 8;
  * N * n_cross_heads * cross width * 2 and t * n_cross_heads * cross width * 2
  * below 2^32; H * N at most 128 * 65535; in bf16 mode at most 128 KV heads. */
 

@@ -408,13 +408,32 @@ template <int N, int I = 0, class F> __device__ __forceinline__ void static_for(
 }
 
 // Fragment loads through a buffer descriptor: one constant offset register
-// per lane, the fragment's byte offset (below 2^32, checked on the host) in a
-// scalar register.  The descriptor spans 4 GiB; callers stay in bounds.
+// per lane, the fragment's byte offset in a scalar register.  The descriptor
+// spans 4 GiB; callers stay in bounds.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00027000);
 }
 __device__ __forceinline__ half8 buf_load_frag(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
   return __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+}
+
+// Where a wave finds its fragments.  One head's keys and values can span more
+// than the 4 GiB of an offset, so the bases are formed in 64 bits: K of a key
+// block from the wave's first key tile in it (tile0, clamped to the last tile;
+// up to four tiles of 64 dc bytes follow: dc below 2^24), X^T from the wave's
+// first feature tile (up to four of 64 npad bytes: npad below 2^24).  Bases in
+// halfs from the head's first, offsets in bytes from the base.
+__host__ __device__ __forceinline__ unsigned xatt_ktile0(unsigned n, unsigned ktlast) {
+  return (n >> 5) < ktlast ? n >> 5 : ktlast;
+}
+__host__ __device__ __forceinline__ long xatt_kbase(unsigned tile0, unsigned ksteps) { return (long)tile0 * ksteps * 512; }
+__host__ __device__ __forceinline__ unsigned xatt_koff(unsigned tile0, unsigned ktlast, unsigned kt, unsigned ksteps,
+                                                       unsigned js) {
+  return ((kt < ktlast - tile0 ? kt : ktlast - tile0) * ksteps + js) * 1024u;
+}
+__host__ __device__ __forceinline__ long xatt_xbase(unsigned ft0, unsigned nsteps) { return (long)ft0 * nsteps * 512; }
+__host__ __device__ __forceinline__ unsigned xatt_xoff(unsigned f, unsigned nsteps, unsigned ns) {
+  return (f * nsteps + (ns < nsteps - 1 ? ns : nsteps - 1)) * 1024u;
 }
 
 template <int TT, int D2, bool TRACK, int KT>
@@ -466,7 +485,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const unsigned ksteps = (unsigned)(a.dc >> 4);   // width steps of one key tile
   const unsigned nsteps = (unsigned)(a.npad >> 4); // key steps of one feature tile
   const unsigned ktlast = (unsigned)(a.npad >> 5) - 1;
-  const __amdgpu_buffer_rsrc_t krsrc = buf_rsrc(kb), xrsrc = buf_rsrc(xtb);
+  const __amdgpu_buffer_rsrc_t xrsrc = buf_rsrc(xtb + xatt_xbase((unsigned)(FW / 32 * w), nsteps));
   const unsigned voff = 16u * (unsigned)lane;
 
   float m_run[LT], l_run[LT];
@@ -547,15 +566,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   auto lds_barrier = [&]() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   };
-  // K fragment of this wave's key tile kt of the block at n0, width step js
-  auto load_k = [&](int n0, int kt, int js) -> half8 {
-    const unsigned kti = min((unsigned)(n0 + KW * w + 32 * kt) >> 5, ktlast);
-    return buf_load_frag(krsrc, voff, (kti * ksteps + (unsigned)js) * 1024u);
+  // the wave's K fragments: of the block at n0 (k_block), its key tile kt, width step js
+  unsigned ktile0 = xatt_ktile0((unsigned)(nbeg + KW * w), ktlast);
+  __amdgpu_buffer_rsrc_t krsrc = buf_rsrc(kb + xatt_kbase(ktile0, ksteps));
+  auto k_block = [&](int n0) {
+    ktile0 = xatt_ktile0((unsigned)(n0 + KW * w), ktlast);
+    krsrc = buf_rsrc(kb + xatt_kbase(ktile0, ksteps));
+  };
+  auto load_k = [&](int kt, int js) -> half8 {
+    return buf_load_frag(krsrc, voff, xatt_koff(ktile0, ktlast, (unsigned)kt, ksteps, (unsigned)js));
   };
   // X^T fragment of this wave's feature tile f, key step ns (absolute)
   auto load_x = [&](int f, int ns) -> half8 {
-    const unsigned ft = (unsigned)(FW / 32 * w + f);
-    return buf_load_frag(xrsrc, voff, (ft * nsteps + min((unsigned)ns, nsteps - 1)) * 1024u);
+    return buf_load_frag(xrsrc, voff, xatt_xoff((unsigned)f, nsteps, (unsigned)ns));
   };
   // key step ps of pass hf of the block at n0: pass hf covers keys
   // [64 hf, 64 hf + 64) of every wave
@@ -576,7 +599,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
   for (int j = 0; j < KR; ++j)
 #pragma unroll
-    for (int kt = 0; kt < KT; ++kt) kr[j][kt] = load_k(nbeg, kt, j);
+    for (int kt = 0; kt < KT; ++kt) kr[j][kt] = load_k(kt, j);
 #pragma unroll
   for (int i = 0; i < RKI; ++i) {
     const int n = nbeg + tid + NT * i;
@@ -622,7 +645,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
               acc_mfma<OT + lt * (KT - KV) + kt - KV>(ak, bq);
             }
           });
-          if (!(decltype(last)::value && j + KR >= NS)) kr[j % KR][kt] = load_k(n0, kt, ch * NS + j + KR);
+          if (!(decltype(last)::value && j + KR >= NS)) kr[j % KR][kt] = load_k(kt, ch * NS + j + KR);
           __builtin_amdgcn_sched_barrier(0);
         });
       }
@@ -783,6 +806,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
     for (int lt = 0; lt < LT; ++lt) psum[lt] = 0.f;
 
+    if (next_block) k_block(n0 + KB);   // (every K load of this block has been issued)
     static_for<NH>([&](auto hfc) {
       constexpr int hf = decltype(hfc)::value;
       // ---- probabilities of the pass's keys
@@ -846,7 +870,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                    // very end: loaded, never used)
 #pragma unroll
             for (int i = KR * KT * ((ps + XR - PS) * FT + f) / (XR * FT); i < KR * KT * ((ps + XR - PS) * FT + f + 1) / (XR * FT); ++i)
-              kr[i / KT][i % KT] = load_k(next_block ? n0 + KB : n0, i % KT, i / KT);
+              kr[i / KT][i % KT] = load_k(i % KT, i / KT);
           }
           __builtin_amdgcn_sched_barrier(0);
         });

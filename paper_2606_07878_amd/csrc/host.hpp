@@ -242,9 +242,11 @@ inline still_status make_dims(const still_config* c, int64_t N, int32_t t, Dims*
     return fail(STILL_E_UNSUPPORTED, "self head width %d must be a multiple of %d", m->ds, GEMM_BN);
   if (m->D % 8) return fail(STILL_E_UNSUPPORTED, "latent_dim %d must be a multiple of 8", m->D);
   if (m->F % 8) return fail(STILL_E_UNSUPPORTED, "ffn_hidden %d must be a multiple of 8", m->F);
-  // the fp16 cross-attention addresses one head's q, k and X^T with 32-bit offsets
+  // the fp16 cross-attention addresses the queries of one head, and key tiles
+  // of one wave (xatt_koff), with 32-bit offsets
   if ((double)N * m->nc * m->dc * 2.0 >= 4294967296.0 || (double)t * m->nc * m->dc * 2.0 >= 4294967296.0)
     return fail(STILL_E_UNSUPPORTED, "N or t too large for one head's 4 GiB key/query span");
+  if (m->dc >= 1 << 24) return fail(STILL_E_UNSUPPORTED, "cross head width %d must be below 2^24", m->dc);
   if (!m->fp32 && m->H > 128) return fail(STILL_E_UNSUPPORTED, "n_kv_heads %d > 128 unsupported", m->H);
   if ((long)m->H * N > (long)GEMM_BN * 65535L)
     return fail(STILL_E_UNSUPPORTED, "H*N = %lld exceeds the supported %ld rows", (long long)(m->H * N), (long)GEMM_BN * 65535L);

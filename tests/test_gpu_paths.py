@@ -103,3 +103,26 @@ def test_backward_tiles(N, t):
     from tests.test_gpu_backward import _grad_case
     w = configs.shrink(configs.get_workload(1), n_kv_heads=8, n_cross_heads=8)
     _grad_case(w, f"8 x 8 heads N={N} t={t}", N=N, t=t)
+
+
+def test_values_of_a_head_past_4_gib():
+    """6.1 million keys in one head of width 256: its values span 5.9 GiB.  The
+    cache is one of 1024 tokens 6000 times over, which leaves the softmax
+    average as it is; every value feature has an offset of its own."""
+    import numpy as np
+    import torch
+    from paper_2606_07878_amd import binding
+    from tests.helpers import dev_tensor, weights_to_device
+    copies = 6000
+    w = configs.shrink(configs.get_workload(1), head_dim=256, n_kv_heads=1, n_tokens=1024, t=24, logit_scale_cross=0.15)
+    cache, wts = synth.make_cache(w, 0), synth.make_weights(w, 0)
+    off = np.random.default_rng(3).normal(0.0, 3.0, (1, 1, 256))
+    cache["V"] = synth.bf16_bits(synth.as_f64(cache)["V"] + off)
+    ref = run_oracle(w.cfg, cache, wts, w.rope_theta, w.t)
+    K, V = (dev_tensor(cache[n], configs.MODE_BF16).repeat(1, copies, 1) for n in ("K", "V"))
+    pos = torch.from_numpy(cache["positions"]).cuda().repeat(copies)
+    W = weights_to_device(wts, configs.MODE_BF16)
+    Ck, Cv, p = binding.compact_layer(w.cfg, W, K, V, pos, w.rope_theta, w.t)
+    torch.cuda.synchronize()
+    assert_parity((Ck.double().cpu().numpy(), Cv.double().cpu().numpy(), p.cpu().numpy()), ref, BF16_TOL,
+                  "values past 4 GiB")
