@@ -501,8 +501,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // Candidate keys for the logit refinement: every key whose logit lies within
   // REFINE_MARGIN of the running maximum goes to a list of its latent's bucket
   // (wave, lane half), which only this lane writes; keys below that can never
-  // be selected.  ncand[lt]: entries so far (the last slot takes all past the
-  // capacity).
+  // be selected.  ncand[lt]: entries.  A list without room for another block's
+  // candidates (16 KT) is halved: of every pair (i, i + half) the larger stays,
+  // so the list's largest key stays whatever comes before and after it.
   int ncand[LT];
 #pragma unroll
   for (int lt = 0; lt < LT; ++lt) ncand[lt] = 0;
@@ -757,6 +758,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       // Candidates: most 32 x 32 tiles have none and are passed by, then most
       // groups of four.  Padding rows past t (their last row's logits) take
       // none.
+      typedef int i32x2 __attribute__((ext_vector_type(2)));
       static_for<LT>([&](auto ltc) {
         constexpr int lt = decltype(ltc)::value;
         const int li = 32 * lt + l32;
@@ -779,16 +781,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
               for (int u = 0; u < 4; ++u) {
                 if (v[u] > cut) {
-                  const int slot = slot0 + min(ncand[lt], XATT_CAP - 1);
-                  ++ncand[lt];
-                  typedef int i32x2 __attribute__((ext_vector_type(2)));
                   const i32x2 e = {__float_as_int(v[u]), k0 + 8 * jq + u};
-                  __builtin_amdgcn_raw_buffer_store_b64(e, crsrc, 8 * slot, 0, 0);
+                  __builtin_amdgcn_raw_buffer_store_b64(e, crsrc, 8 * (slot0 + ncand[lt]), 0, 0);
+                  ++ncand[lt];
                 }
               }
             }
           });
         });
+        if (__any(ncand[lt] > XATT_CAP - 16 * KT)) {
+          const int n = ncand[lt] > XATT_CAP - 16 * KT ? ncand[lt] : 0, half = (n + 1) / 2;
+          const int at = 8 * (li * XATT_NBK + 2 * w + lg) * XATT_CAP;
+          constexpr int NB = 8;   // pairs loaded at a time
+#pragma unroll 1
+          for (int i = 0; i + half < n; i += NB) {
+            float own[NB];
+            i32x2 other[NB];
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {   // (past the last pair: the last one again)
+              const int p = 8 * min(i + q, n - half - 1);
+              own[q] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(crsrc, at + p, 0, 0));
+              other[q] = __builtin_bit_cast(i32x2, __builtin_amdgcn_raw_buffer_load_b64(crsrc, at + p + 8 * half, 0, 0));
+            }
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
+              if (__int_as_float(other[q].x) > own[q])
+                __builtin_amdgcn_raw_buffer_store_b64(other[q], crsrc, at + 8 * min(i + q, n - half - 1), 0, 0);
+          }
+          if (n) ncand[lt] = half;
+        }
       });
     }
     // rescale O for the latents whose maximum grew (rare after the first

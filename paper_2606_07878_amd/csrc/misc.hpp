@@ -486,18 +486,20 @@ struct CandArgs {
 // within REFINE_MARGIN of the row maximum, largest first, up to R of them:
 // slots [0, rcnt[row]) of the row hold them.  Exact ties (duplicated cache
 // rows) are taken together up to that cap, so their weights stay consistent.
-// More than CAP in-margin entries in a row: the first CAP read are ranked.
 //
 // One wave per row: the lists are read with coalesced loads (LISTS: 8 entries
 // of each list per step), the in-margin candidates (usually two or three) are
 // compacted into LDS, and each takes its rank among them, equal logits
 // ordered by key index, so the selection does not depend on the order in
-// which the fp32 flash pass appended overflow entries.
+// which the fp32 flash pass appended overflow entries.  A row with more than
+// CAP of them counts them by their distance to the maximum, in CAP classes,
+// and compacts the classes that make up the R largest (of the last class as
+// many as there is room for, in reading order).
 template <int R, bool LISTS>
 __global__ __launch_bounds__(256) void refine_select_kernel(CandArgs ca, const float* __restrict__ mpart, int S,
                                                             long HCT, int* __restrict__ ridx, float* __restrict__ rval,
                                                             int* __restrict__ rcnt) {
-  constexpr int CAP = 512;   // in-margin candidates kept per row
+  constexpr int CAP = 512;   // in-margin candidates compacted per row, classes of the count
   __shared__ float sv[4][CAP];
   __shared__ int si[4][CAP];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -509,34 +511,99 @@ __global__ __launch_bounds__(256) void refine_select_kernel(CandArgs ca, const f
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
   const float cut = M - REFINE_MARGIN;
-  int n = 0;
-  if (active) {
+  // f(in margin, logit, key) for all entries, a wave of them at a time (the
+  // loads of UN steps in flight together), until it returns false
+  auto scan = [&](auto un, auto f) {
+    constexpr int UN = decltype(un)::value;
     for (int s = 0; s < S; ++s) {
       const long sr = s * HCT + row;
       const int list = lane >> 3, cnt = LISTS ? ca.cnt[sr * XATT_NBK + list] : ca.CB + ca.cnt[sr];
-      for (int k0 = 0; __any(k0 < cnt); k0 += LISTS ? 8 : 64) {
-        const int k = k0 + (LISTS ? lane & 7 : lane);
-        float v = -INFINITY;
-        int id = -1;
-        if (k < cnt) {
-          if constexpr (LISTS) {
-            const float2 e = ca.cand[(sr * XATT_NBK + list) * XATT_CAP + k];
-            v = e.x;
-            id = __float_as_int(e.y);
-          } else {
-            v = ca.cval[sr * ca.C + k];
-            id = ca.cidx[sr * ca.C + k];
+      for (int k0 = 0; __any(k0 < cnt); k0 += UN * (LISTS ? 8 : 64)) {
+        float v[UN];
+        int id[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+          const int k = k0 + (LISTS ? 8 * u + (lane & 7) : 64 * u + lane);
+          v[u] = -INFINITY;
+          id[u] = -1;
+          if (k < cnt) {
+            if constexpr (LISTS) {
+              const float2 e = ca.cand[(sr * XATT_NBK + list) * XATT_CAP + k];
+              v[u] = e.x;
+              id[u] = __float_as_int(e.y);
+            } else {
+              v[u] = ca.cval[sr * ca.C + k];
+              id[u] = ca.cidx[sr * ca.C + k];
+            }
           }
         }
-        const bool keep = id >= 0 && v >= cut;
-        const unsigned long long mask = __ballot(keep);
-        const int pos = n + __popcll(mask & ((1ull << lane) - 1ull));
-        if (keep && pos < CAP) {
-          sv[wv][pos] = v;
-          si[wv][pos] = id;
-        }
-        n += __popcll(mask);
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+          if (!f(id[u] >= 0 && v[u] >= cut, v[u], id[u])) return;
       }
+    }
+  };
+  int n = 0;
+  auto put = [&](bool keep, float v, int id, int& at) {   // at: the next place, the same in every lane
+    const unsigned long long mask = __ballot(keep);
+    const int pos = at + __popcll(mask & ((1ull << lane) - 1ull));
+    if (keep && pos < CAP) {
+      sv[wv][pos] = v;
+      si[wv][pos] = id;
+    }
+    at += __popcll(mask);
+  };
+  if (active) {
+    scan(std::integral_constant<int, 1>{}, [&](bool keep, float v, int id) {
+      put(keep, v, id, n);
+      return n <= CAP;
+    });
+    if (n > CAP) {   // (only this wave touches its arrays)
+      auto cls = [&](float v) { return min(max((int)((M - v) * (CAP / REFINE_MARGIN)), 0), CAP - 1); };
+      __threadfence_block();
+      for (int q = lane; q < CAP; q += 64) si[wv][q] = 0;
+      __threadfence_block();
+      scan(std::integral_constant<int, 4>{}, [&](bool keep, float v, int) {
+        if (keep) atomicAdd(&si[wv][cls(v)], 1);
+        return true;
+      });
+      __threadfence_block();
+      // each lane adds up CAP / 64 classes: the first `full` ones hold `whole` <= R keys, one class more would not
+      constexpr int PL = CAP / 64;
+      int own = 0;
+#pragma unroll
+      for (int q = 0; q < PL; ++q) own += si[wv][PL * lane + q];
+      int sum = own;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(sum, o);
+        sum += lane >= o ? x : 0;
+      }
+      sum -= own;
+      int full = 0, whole = 0;
+#pragma unroll
+      for (int q = 0; q < PL; ++q) {
+        sum += si[wv][PL * lane + q];
+        if (sum <= R) {
+          ++full;
+          whole = sum;
+        }
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        full += __shfl_xor(full, o);
+        whole = max(whole, __shfl_xor(whole, o));
+      }
+      __threadfence_block();
+      n = 0;
+      int last = whole;
+      scan(std::integral_constant<int, 4>{}, [&](bool keep, float v, int id) {
+        const int c = cls(v);
+        put(keep && c < full, v, id, n);
+        put(keep && c == full, v, id, last);
+        return true;
+      });
+      n = last;
     }
   }
   n = min(n, CAP);

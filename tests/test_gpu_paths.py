@@ -126,3 +126,50 @@ def test_values_of_a_head_past_4_gib():
     torch.cuda.synchronize()
     assert_parity((Ck.double().cpu().numpy(), Cv.double().cpu().numpy(), p.cpu().numpy()), ref, BF16_TOL,
                   "values past 4 GiB")
+
+
+def _three_level_layer(levels, seed=5):
+    """A one-block compactor with H = 2, nc = 8 and a cache in which the key
+    n's logits lie about levels[n] log2 units below the largest, for every
+    latent: the projections are a bias of two large components plus noise, and
+    keys lean away from it by an angle that their level sets.  Keys rounded to
+    fp16 move such a logit by some 0.1 log2 units, each by its own amount."""
+    import numpy as np
+    H, d, nc, dc, t, D = 2, 128, 8, 128, 1024, 128
+    N = len(levels)
+    w = configs.shrink(configs.get_workload(1), head_dim=d, n_kv_heads=H, n_tokens=N, t=t, latent_dim=D,
+                       n_cross_heads=nc, n_self_heads=0, ffn_kind=configs.FFN_NONE, ffn_hidden=0,
+                       logit_scale_cross=1024.0)
+    r = np.random.default_rng(seed)
+    wts = synth.make_weights(w, 0)
+    e, g = np.zeros(dc), np.zeros(dc)
+    e[[3, 5]], g[[20, 21]] = np.sqrt(0.5), np.sqrt(0.5)
+    lean = np.sqrt(np.maximum(2 * np.asarray(levels) / (1024 * np.log2(np.e)), 0.0))   # 1 - cos = lean^2 / 2
+    K = np.zeros((H, N, d))
+    K[:, :, 0] = lean
+    wk = r.normal(0.0, 1.5e-4, (nc, dc, 2 * d))
+    wk[:, :, :d] = 0.0
+    wk[:, :, 0] = g
+    bits = synth.bf16_bits
+    wts["b0.ca_wk"] = bits(wk.reshape(nc * dc, 2 * d))
+    wq = r.normal(0.0, 1.5e-4, (nc, dc, D))
+    wq[:, [3, 5]] = 0.0                         # the large components of q are exact in fp16
+    wts["b0.ca_wq"] = bits(wq.reshape(nc * dc, D))
+    wts["b0.ca_bq"] = wts["b0.ca_bk"] = bits(np.tile(e, nc))
+    cache = dict(K=bits(K), V=bits(r.standard_normal((H, N, d))), positions=np.zeros(N))
+    return w, cache, wts
+
+
+def test_heaviest_keys_among_full_candidate_lists():
+    """Sixteen keys carry the mass of every latent.  In their key split they
+    come after many thousand keys that were candidates at the time and before
+    some 3500 that stay within the refinement margin: neither may displace them."""
+    import numpy as np
+    N = 65536
+    levels = np.full(N, 12.5)                   # below the margin once the heavy keys are seen
+    levels[N - 3584:] = 9.6                     # within it
+    levels[N - 3600:N - 3584] = 0.0             # the heavy keys
+    w, cache, wts = _three_level_layer(levels)
+    ref = run_oracle(w.cfg, cache, wts, w.rope_theta, w.t, heads=[1])
+    got = run_gpu(w.cfg, cache, wts, w.rope_theta, w.t)
+    assert_parity((got[0][1:], got[1][1:], got[2]), ref, BF16_TOL, "full candidate lists")
