@@ -39,10 +39,10 @@
  *   10 log2 units of its latent's maximum is then recomputed accurately (fp32
  *   from split fp16 operands, or fp64) and its weight replaced.  Capacity: the
  *   256 largest such keys per latent, from at most 1536 (fp32 mode) or 8 lists
- *   of 512 (bf16 mode) candidates per latent and key split.  A bf16-mode list
- *   that fills keeps the larger of every two entries, so that the largest key
- *   of a latent is always recomputed.  Caches with more near-maximal keys per
- *   latent (rows repeated hundreds of times) lose accuracy gradually.
+ *   of 192 (bf16 mode) candidates per latent and key split.  A bf16-mode list
+ *   that fills keeps its largest entries, so that the largest key of a latent
+ *   is always recomputed.  Caches with more near-maximal keys per latent (rows
+ *   repeated hundreds of times) lose accuracy gradually.
  * - Work is enqueued on `stream` (NULL = default stream) and the call returns
  *   without synchronising.  Arguments are validated before anything is
  *   enqueued; a non-OK status means nothing was launched.  Faults during

@@ -450,7 +450,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   constexpr int QI = TT / 8 / NW;        // Q stage loads per wave and chunk (8 rows of 128 bytes each)
   constexpr int PB = 256, NH = KB / PB;  // keys per P.X pass, passes per block
   constexpr int LP = PB + 8;             // P row stride (halfs)
-  static_assert(XATT_NBK == 2 * NW, "one candidate list per wave and lane half");
+  static_assert(XATT_NBK == 2 * NW && XATT_CAP < 256 && XATT_CAP >= 32 * KT, "one candidate list per wave and lane half");
   constexpr int XR = FT >= 4 ? 2 : 4;    // X^T ring depth (key steps of 16)
   constexpr int PS = PB / 16;            // key steps per P.X pass
   constexpr int RKI = KB / NT;           // key norms loaded per thread and block
@@ -501,12 +501,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // Candidate keys for the logit refinement: every key whose logit lies within
   // REFINE_MARGIN of the running maximum goes to a list of its latent's bucket
   // (wave, lane half), which only this lane writes; keys below that can never
-  // be selected.  ncand[lt]: entries.  A list without room for another block's
-  // candidates (16 KT) is halved: of every pair (i, i + half) the larger stays,
-  // so the list's largest key stays whatever comes before and after it.
-  int ncand[LT];
+  // be selected.  A list without room for another block's candidates (16 KT)
+  // keeps the entries that reach the mean of 32 of them, and of these, if they are still too
+  // many, the larger of every pair (i, i + half): its largest keys stay whatever
+  // comes before and after them.  Keys below that mean enter no more: where all
+  // keys lie within the margin the scattered stores of the entries would take
+  // longer than the products (32768 keys, 256 latents, 8 x 8 heads, logits
+  // scaled by 1, whole layer: 15.5 ms with lists of 512 that only halve, 13.0
+  // now).  ncand[lt]: entries
+  // (low 8 bits) and that mean, rounded down (-inf before the first time).
+  unsigned ncand[LT];
 #pragma unroll
-  for (int lt = 0; lt < LT; ++lt) ncand[lt] = 0;
+  for (int lt = 0; lt < LT; ++lt) ncand[lt] = 0xff800000u;
   const __amdgpu_buffer_rsrc_t crsrc =   // the lists of the tile's first row
       buf_rsrc(TRACK ? a.cand + (((long)split * HC + hc) * a.t + t0) * (XATT_NBK * XATT_CAP) : nullptr);
   acc_reserve();
@@ -762,7 +768,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       static_for<LT>([&](auto ltc) {
         constexpr int lt = decltype(ltc)::value;
         const int li = 32 * lt + l32;
-        const float cut = t0 + li < a.t ? m_run[lt] - REFINE_MARGIN : INFINITY;
+        int n = (int)(ncand[lt] & 0xffu);
+        const float cut = t0 + li < a.t ? fmaxf(m_run[lt] - REFINE_MARGIN, __uint_as_float(ncand[lt] & ~0xffu)) : INFINITY;
         static_for<KT>([&](auto ktc) {
           constexpr int kt = decltype(ktc)::value;
           if (!__any(lmx[lt][kt] * qs[lt] > cut)) return;
@@ -782,33 +789,69 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
               for (int u = 0; u < 4; ++u) {
                 if (v[u] > cut) {
                   const i32x2 e = {__float_as_int(v[u]), k0 + 8 * jq + u};
-                  __builtin_amdgcn_raw_buffer_store_b64(e, crsrc, 8 * (slot0 + ncand[lt]), 0, 0);
-                  ++ncand[lt];
+                  __builtin_amdgcn_raw_buffer_store_b64(e, crsrc, 8 * (slot0 + n), 0, 0);
+                  ++n;
                 }
               }
             }
           });
         });
-        if (__any(ncand[lt] > XATT_CAP - 16 * KT)) {
-          const int n = ncand[lt] > XATT_CAP - 16 * KT ? ncand[lt] : 0, half = (n + 1) / 2;
+        ncand[lt] = (ncand[lt] & ~0xffu) | (unsigned)n;
+        constexpr int MOST = XATT_CAP - 16 * KT, NB = 8;   // NB: entries loaded at a time
+        if (__any(n > MOST)) {
+          n = n > MOST ? n : 0;
           const int at = 8 * (li * XATT_NBK + 2 * w + lg) * XATT_CAP;
-          constexpr int NB = 8;   // pairs loaded at a time
+          float sum = 0.f, top = -INFINITY;
 #pragma unroll 1
-          for (int i = 0; i + half < n; i += NB) {
-            float own[NB];
-            i32x2 other[NB];
-#pragma unroll
-            for (int q = 0; q < NB; ++q) {   // (past the last pair: the last one again)
-              const int p = 8 * min(i + q, n - half - 1);
-              own[q] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(crsrc, at + p, 0, 0));
-              other[q] = __builtin_bit_cast(i32x2, __builtin_amdgcn_raw_buffer_load_b64(crsrc, at + p + 8 * half, 0, 0));
-            }
+          for (int i = 0; i < 32; i += NB) {
+            float x[NB];
 #pragma unroll
             for (int q = 0; q < NB; ++q)
-              if (__int_as_float(other[q].x) > own[q])
-                __builtin_amdgcn_raw_buffer_store_b64(other[q], crsrc, at + 8 * min(i + q, n - half - 1), 0, 0);
+              x[q] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(crsrc, at + 8 * ((i + q) * n >> 5), 0, 0));
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+              sum += x[q];
+              top = fmaxf(top, x[q]);
+            }
           }
-          if (n) ncand[lt] = half;
+          const float mean = fminf(sum * (1.f / 32), top);
+          int kept = 0;
+#pragma unroll 1
+          for (int i = 0; i < n; i += NB) {   // (kept <= i: no entry is overwritten before it is read)
+            i32x2 e[NB];
+#pragma unroll
+            for (int q = 0; q < NB; ++q)   // (past the last entry: the last one again)
+              e[q] = __builtin_bit_cast(i32x2, __builtin_amdgcn_raw_buffer_load_b64(crsrc, at + 8 * min(i + q, n - 1), 0, 0));
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
+              if (i + q < n && __int_as_float(e[q].x) >= mean) {
+                __builtin_amdgcn_raw_buffer_store_b64(e[q], crsrc, at + 8 * kept, 0, 0);
+                ++kept;
+              }
+          }
+          if (__any(kept > MOST)) {
+            const int m = kept > MOST ? kept : 0, half = (m + 1) / 2;
+#pragma unroll 1
+            for (int i = 0; i + half < m; i += NB) {
+              float own[NB];
+              i32x2 other[NB];
+#pragma unroll
+              for (int q = 0; q < NB; ++q) {
+                const int p = at + 8 * min(i + q, m - half - 1);
+                own[q] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(crsrc, p, 0, 0));
+                other[q] = __builtin_bit_cast(i32x2, __builtin_amdgcn_raw_buffer_load_b64(crsrc, p + 8 * half, 0, 0));
+              }
+#pragma unroll
+              for (int q = 0; q < NB; ++q)
+                if (__int_as_float(other[q].x) > own[q])
+                  __builtin_amdgcn_raw_buffer_store_b64(other[q], crsrc, at + 8 * min(i + q, m - half - 1), 0, 0);
+            }
+            kept = m ? half : kept;
+          }
+          if (n) {   // (every entry is above the mean before, but for its rounding)
+            const unsigned u = __float_as_uint(mean), down = mean < 0.f ? u + 0xffu : u;
+            ncand[lt] = (down & ~0xffu) | (unsigned)kept;
+          }
         }
       });
     }
@@ -931,7 +974,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       a.mpart[row] = m_run[lt];
       a.lpart[row] = l_run[lt];
     }
-    if constexpr (TRACK) a.ocnt[row * XATT_NBK + 2 * w + lg] = min(ncand[lt], XATT_CAP);
+    if constexpr (TRACK) a.ocnt[row * XATT_NBK + 2 * w + lg] = (int)(ncand[lt] & 0xffu);
   });
 }
 

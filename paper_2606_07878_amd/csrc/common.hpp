@@ -145,9 +145,8 @@ constexpr float REFINE_MARGIN = 10.f;
 // Candidate lists of the fp16 cross-attention per (split, latent row): one per
 // (wave, lane half) of its workgroup, each written by one lane, so that no
 // candidate is counted through shared memory and the lists do not depend on
-// the order of the waves.  A run of equal keys falls to one wave, so a list
-// holds far more than an even share of the in-margin keys.
-constexpr int XATT_NBK = 8, XATT_CAP = 512;
+// the order of the waves.
+constexpr int XATT_NBK = 8, XATT_CAP = 192;
 
 template <class CT> __device__ __forceinline__ typename Mma<CT>::frag zero_frag() {
   typename Mma<CT>::frag z;

@@ -173,3 +173,15 @@ def test_heaviest_keys_among_full_candidate_lists():
     ref = run_oracle(w.cfg, cache, wts, w.rope_theta, w.t, heads=[1])
     got = run_gpu(w.cfg, cache, wts, w.rope_theta, w.t)
     assert_parity((got[0][1:], got[1][1:], got[2]), ref, BF16_TOL, "full candidate lists")
+
+
+@pytest.mark.parametrize("scale", [0.2, 2.0, 30.0])
+def test_logit_scales_that_fill_the_candidate_lists(scale):
+    """Logit scales at which all keys (0.2, 2) or hundreds (30) lie within the
+    refinement margin: lists of 1024 keys each are halved time and again."""
+    w = configs.shrink(configs.get_workload(1), head_dim=128, n_kv_heads=2, n_tokens=16384, t=1024, n_cross_heads=8,
+                       n_self_heads=0, logit_scale_cross=scale)
+    cache, wts = synth.make_cache(w, 0), synth.make_weights(w, 0)
+    ref = run_oracle(w.cfg, cache, wts, w.rope_theta, w.t, heads=[1])
+    got = run_gpu(w.cfg, cache, wts, w.rope_theta, w.t)
+    assert_parity((got[0][1:], got[1][1:], got[2]), ref, BF16_TOL, f"scale {scale}")
