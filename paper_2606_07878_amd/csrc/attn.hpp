@@ -45,7 +45,8 @@ struct AttnArgs {
   float* cval;       // fp32 kernel: [S][H*nc][t][ncand] largest logits seen (log2 units) ...
   int* cidx;         // ... and their key indices (-1 = none): 2 TOPK list entries (one list per
                      // lane half), then up to ATT_OVF overflow entries
-  float2* cand;      // fp16 kernel: [S][H*nc][t][XATT_NBK][XATT_CAP] (logit, key index as bits)
+  float2* cand;      // fp16 kernel: [S][H*nc][t][XATT_NBK][ccap] (logit, key index as bits)
+  int ccap;          // XATT_CAP or XATT_CAP_SPLIT
   int* ocnt;         // fp32 kernel: [S][H*nc][t] overflow entries; fp16 kernel: [S][H*nc][t][XATT_NBK] entries
 };
 
@@ -57,7 +58,7 @@ struct AttnArgs {
 // fp32 kernel: overflow entries, in-margin keys that a full register list
 // rejects or evicts.
 constexpr int ATT_OVF = 1536;
-// (The fp16 kernel's lists: XATT_NBK, XATT_CAP, common.hpp.)
+// (The fp16 kernel's lists: common.hpp.)
 
 template <class CT, int TT, int NB, int DK, int D2, int TOPK>
 __global__ __launch_bounds__(256) void cross_attn_kernel(AttnArgs a) {
@@ -450,7 +451,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   constexpr int QI = TT / 8 / NW;        // Q stage loads per wave and chunk (8 rows of 128 bytes each)
   constexpr int PB = 256, NH = KB / PB;  // keys per P.X pass, passes per block
   constexpr int LP = PB + 8;             // P row stride (halfs)
-  static_assert(XATT_NBK == 2 * NW && XATT_CAP < 256 && XATT_CAP >= 32 * KT, "one candidate list per wave and lane half");
+  static_assert(XATT_NBK == 2 * NW && XATT_CAP < 256, "one candidate list per wave and lane half");
+  static_assert(XATT_CAP_SPLIT >= 32 * KT, "room for a block's candidates and as many again");
   constexpr int XR = FT >= 4 ? 2 : 4;    // X^T ring depth (key steps of 16)
   constexpr int PS = PB / 16;            // key steps per P.X pass
   constexpr int RKI = KB / NT;           // key norms loaded per thread and block
@@ -502,19 +504,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // REFINE_MARGIN of the running maximum goes to a list of its latent's bucket
   // (wave, lane half), which only this lane writes; keys below that can never
   // be selected.  A list without room for another block's candidates (16 KT)
-  // keeps the entries that reach the mean of 32 of them, and of these, if they are still too
-  // many, the larger of every pair (i, i + half): its largest keys stay whatever
-  // comes before and after them.  Keys below that mean enter no more: where all
-  // keys lie within the margin the scattered stores of the entries would take
-  // longer than the products (32768 keys, 256 latents, 8 x 8 heads, logits
-  // scaled by 1, whole layer: 15.5 ms with lists of 512 that only halve, 13.0
-  // now).  ncand[lt]: entries
-  // (low 8 bits) and that mean, rounded down (-inf before the first time).
+  // keeps the entries that reach the mean of 32 of them and of these, if they
+  // are still too many, the larger of every pair (i, i + half): its largest keys
+  // stay whatever comes before and after them.  Keys below that mean enter no
+  // more: where all keys lie within the margin the scattered stores of the
+  // entries would take longer than the products (32768 keys, 256 latents, 8 x 8
+  // heads, logits scaled by 1, whole layer: 15.5 ms with lists of 512 that only
+  // halve, 13.0 now).  ncand[lt]: entries (low 8 bits) and that mean, rounded
+  // down (-inf before the first time).
   unsigned ncand[LT];
 #pragma unroll
   for (int lt = 0; lt < LT; ++lt) ncand[lt] = 0xff800000u;
   const __amdgpu_buffer_rsrc_t crsrc =   // the lists of the tile's first row
-      buf_rsrc(TRACK ? a.cand + (((long)split * HC + hc) * a.t + t0) * (XATT_NBK * XATT_CAP) : nullptr);
+      buf_rsrc(TRACK ? a.cand + (((long)split * HC + hc) * a.t + t0) * (XATT_NBK * a.ccap) : nullptr);
   acc_reserve();
   static_for<16 * OT>([&](auto r) { acc_write<decltype(r)::value>(0.f); });
 
@@ -775,7 +777,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           if (!__any(lmx[lt][kt] * qs[lt] > cut)) return;
           acc_reserve();
           asm volatile("" : "+v"(lg));   // (norms and masks are read anew, not kept from the pass before)
-          const int slot0 = (li * XATT_NBK + 2 * w + lg) * XATT_CAP, k0 = n0 + KW * w + 32 * kt + 4 * lg;
+          const int slot0 = (li * XATT_NBK + 2 * w + lg) * a.ccap, k0 = n0 + KW * w + 32 * kt + 4 * lg;
           static_for<4>([&](auto jqc) {
             constexpr int jq = decltype(jqc)::value;
             float rk[4], kb[4], v[4];
@@ -797,10 +799,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           });
         });
         ncand[lt] = (ncand[lt] & ~0xffu) | (unsigned)n;
-        constexpr int MOST = XATT_CAP - 16 * KT, NB = 8;   // NB: entries loaded at a time
-        if (__any(n > MOST)) {
-          n = n > MOST ? n : 0;
-          const int at = 8 * (li * XATT_NBK + 2 * w + lg) * XATT_CAP;
+        const int most = a.ccap - 16 * KT;
+        if (__any(n > most)) {
+          constexpr int NB = 8;   // entries loaded at a time
+          n = n > most ? n : 0;
+          const int at = 8 * (li * XATT_NBK + 2 * w + lg) * a.ccap;
           float sum = 0.f, top = -INFINITY;
 #pragma unroll 1
           for (int i = 0; i < 32; i += NB) {
@@ -829,8 +832,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 ++kept;
               }
           }
-          if (__any(kept > MOST)) {
-            const int m = kept > MOST ? kept : 0, half = (m + 1) / 2;
+          if (__any(kept > most)) {
+            const int m = kept > most ? kept : 0, half = (m + 1) / 2;
 #pragma unroll 1
             for (int i = 0; i + half < m; i += NB) {
               float own[NB];

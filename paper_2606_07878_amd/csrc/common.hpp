@@ -146,7 +146,10 @@ constexpr float REFINE_MARGIN = 10.f;
 // (wave, lane half) of its workgroup, each written by one lane, so that no
 // candidate is counted through shared memory and the lists do not depend on
 // the order of the waves.
-constexpr int XATT_NBK = 8, XATT_CAP = 192;
+// Entries per list: 192, or 128 where the splits can be twice as many as two
+// workgroups per CU take (host.hpp), so that the lists of a latent take at most
+// a third more than 192 entries in half the splits would.
+constexpr int XATT_NBK = 8, XATT_CAP = 192, XATT_CAP_SPLIT = 128;
 
 template <class CT> __device__ __forceinline__ typename Mma<CT>::frag zero_frag() {
   typename Mma<CT>::frag z;

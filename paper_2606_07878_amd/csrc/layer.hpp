@@ -134,18 +134,7 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
   const double* invf_b = (const double*)(ws + p.invf_b);
   const float2* tab_bq = (const float2*)(ws + p.tab_bq);
   const float LOG2E = 1.4426950408889634f;
-  // Refinement of the near-maximal logits of the cross-attention.  The
-  // QK-norm bounds every logit by the scale, so a rounding of q or k by a
-  // relative u moves a logit (log2 units) by at most 2 u ca_log2 and a weight
-  // by 2 ln2 u ca_log2.  Up to ca_log2 = 1/4 that is below half a rounding of
-  // the weight itself (u = 2^-11 in fp16, 2^-24 in fp32), while every key lies
-  // within the margin of its row's maximum: the candidate lists would fill
-  // with keys whose exact logits change nothing.  One 8k -> 1024 layer of the
-  // two-block compactor of width 256 at logits scaled by 1/16: 4.7 ms with
-  // the refinement (850 us per block in its kernel alone), 0.77 ms without;
-  // same distance to the exact result.
   const float ca_scale = cfg->logit_scale_cross != 0.f ? cfg->logit_scale_cross : (float)m.dc;
-  const bool refine = m.R > 0 && !(ca_scale * LOG2E <= 0.25f);
   // wide GEMM tiles for the paired projections when the head widths allow them
   const bool wide_c = !m.fp32 && m.dc % 256 == 0, wide_s = !m.fp32 && m.ns > 0 && m.ds % 256 == 0;
 
@@ -253,16 +242,15 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
     // ---------------- cross-attention: Z += CrossAttn(RMSNorm(Z), X)
     if (cfg->cross_every_block || b == 0) {
       if constexpr (sizeof(CT) == 2) {
-        if (m.R > 0 && !m.fp32) HIP_TRY(rmsnorm_split(Y, (CT*)(ws + p.Ylo)));
-        else HIP_TRY(rmsnorm());
+        HIP_TRY(rmsnorm_split(Y, (CT*)(ws + p.Ylo)));
       } else {
         HIP_TRY(rmsnorm());
       }
       {  // q = RoPE_c(q~) with q~ = Y W_Q^T + b_Q, plus ||q~||^2 partials
         GemmArgs g = gargs((int)Ht, m.Ec / 2, m.D, Y, m.D, bw.ca_wq, m.D, q, m.Ec);
-        if (m.R > 0 && !m.fp32) {   // Y split into hi + lo: accurate q~ (fp32 copy for the refinement)
+        if (!m.fp32) {   // Y split into hi + lo: accurate q~ (fp32 copy for the refinement)
           g.A2 = ws + p.Ylo;
-          if (refine) g.C2 = (float*)(ws + p.qex);
+          if (m.refine) g.C2 = (float*)(ws + p.qex);
         }
         g.bias = bw.ca_bq;
         g.hd = m.dc;
@@ -362,16 +350,17 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
         a.d2 = m.d2;
         a.scale_log2 = ca_scale * LOG2E;
         a.keys_per_split = (int)m.keys_per_split;
-        a.cval = m.fp32 ? (float*)(ws + p.cval) : nullptr;
-        a.cidx = m.fp32 ? (int*)(ws + p.cidx) : nullptr;
-        a.cand = m.fp32 ? nullptr : (float2*)(ws + p.cand);
-        a.ocnt = (int*)(ws + p.ocnt);
+        a.cval = m.refine && m.fp32 ? (float*)(ws + p.cval) : nullptr;
+        a.cidx = m.refine && m.fp32 ? (int*)(ws + p.cidx) : nullptr;
+        a.cand = m.refine && !m.fp32 ? (float2*)(ws + p.cand) : nullptr;
+        a.ccap = m.ncand;
+        a.ocnt = m.refine ? (int*)(ws + p.ocnt) : nullptr;
         a.xfeat = m.d2;
         a.xcoff = 0;
         hipError_t e;
         {
         TIMED(STILL_K_CROSS_ATTN);
-        if (!refine) {
+        if (!m.refine) {
           if (m.d2 == 128) e = launch_attn<CT, 128, false>(a, m.splits, st);
           else if (m.d2 == 256) e = launch_attn<CT, 256, false>(a, m.splits, st);
           else e = launch_attn<CT, 512, false>(a, m.splits, st);
@@ -382,7 +371,7 @@ still_status run_layer(const still_config* cfg, const Dims& m, const Plan& p, ch
         HIP_TRY(e);
         RefineArgs ra;
         memset(&ra, 0, sizeof ra);
-        if (refine) {
+        if (m.refine) {
           const long HCT = Ht * m.nc;
           const int TR = m.t * m.R, NB = m.H * m.nc;
           int* ridx = (int*)(ws + p.ridx);

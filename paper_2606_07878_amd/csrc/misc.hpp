@@ -472,7 +472,7 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(const float* __restri
 
 // The candidate lists of the flash pass, per (split, latent row): fp32 kernel
 // C entries, CB fixed ones then cnt[split][row] overflow entries; fp16 kernel
-// XATT_NBK lists of up to XATT_CAP (logit, key) pairs, cnt[split][row][list]
+// XATT_NBK lists of up to C (logit, key) pairs, cnt[split][row][list]
 // of them filled.
 struct CandArgs {
   const float* cval;
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(256) void refine_select_kernel(CandArgs ca, const f
           id[u] = -1;
           if (k < cnt) {
             if constexpr (LISTS) {
-              const float2 e = ca.cand[(sr * XATT_NBK + list) * XATT_CAP + k];
+              const float2 e = ca.cand[(sr * XATT_NBK + list) * ca.C + k];
               v[u] = e.x;
               id[u] = __float_as_int(e.y);
             } else {
