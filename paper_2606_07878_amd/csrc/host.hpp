@@ -274,7 +274,7 @@ inline still_status make_dims(const still_config* c, int64_t N, int32_t t, Dims*
   // and C_v (bf16) and the fp32 mode's outputs equal to 0.5 %, the fp32 bias
   // values within the spread of the seeds (ratio 0.95 - 1.06, mean 1.00).
   const float ca_scale = c->logit_scale_cross != 0.f ? c->logit_scale_cross : (float)m->dc;
-  m->refine = !(ca_scale * 1.4426950408889634f <= 0.25f);
+  m->refine = !(fabsf(ca_scale) * 1.4426950408889634f <= 0.25f);
   m->att_tt = m->fp32 ? 128 : xatt_tt(t);
   choose_splits(m);
   m->keys_per_split = rup((m->N + m->splits - 1) / m->splits, key_block(*m));

@@ -185,3 +185,10 @@ def test_logit_scales_that_fill_the_candidate_lists(scale):
     ref = run_oracle(w.cfg, cache, wts, w.rope_theta, w.t, heads=[1])
     got = run_gpu(w.cfg, cache, wts, w.rope_theta, w.t)
     assert_parity((got[0][1:], got[1][1:], got[2]), ref, BF16_TOL, f"scale {scale}")
+
+
+def test_negative_logit_scale_fp32():
+    """fp32 mode at a scale of -1024: the near-maximal logits are recomputed as
+    at +1024."""
+    w = configs.shrink(configs.get_workload(1), logit_scale_cross=-1024.0)
+    _layer_case(w, configs.MODE_FP32, 1000, 130, "scale -1024")

@@ -38,3 +38,10 @@ def test_no_refinement_buffers_without_refinement(mode, gb):
                               n_cross_heads=1, n_self_heads=1, ffn_kind=configs.FFN_NONE, ffn_hidden=0)
     assert _size(cfg, 8192, 1024, mode, logit_scale_cross=1 / 16) <= gb * 1e9
     assert _size(cfg, 8192, 1024, mode, logit_scale_cross=1.0) > 3 * gb * 1e9 / 1.2
+
+
+@pytest.mark.parametrize("mode", [configs.MODE_BF16, configs.MODE_FP32])
+def test_refinement_rule_takes_the_magnitude_of_the_scale(mode):
+    cfg = configs.get_workload(1).cfg
+    assert (_size(cfg, 2048, 256, mode, logit_scale_cross=-1024.0) == _size(cfg, 2048, 256, mode, logit_scale_cross=1024.0)
+            > _size(cfg, 2048, 256, mode, logit_scale_cross=-0.1) == _size(cfg, 2048, 256, mode, logit_scale_cross=0.1))
