@@ -231,7 +231,8 @@ typedef struct {
   double rope_theta;    /* > 0: rotate q at q_positions; 0: q used as given     */
 } still_attend_config;
 
-/* Bytes of device workspace still_attend needs (0: invalid configuration). */
+/* Bytes of device workspace that serve still_attend at this configuration and
+ * at every smaller t and n_suffix (0: invalid configuration). */
 size_t still_attend_workspace_size(const still_attend_config *cfg);
 
 /*   q          [H*group][n_queries][d]  (query head h*group + g uses KV head h)

@@ -152,15 +152,16 @@ static still_status attend_plan(const still_attend_config* c, AttendPlan* ap) {
     return at->lpart + rup((long)(slots * sizeof(float)), 256) + 256;   // + alignment slack
   };
   ap->need = bytes(ap->splits, ap);
-  // The size reported is that of one-wave splits at every row count, which a
-  // buffer sized for a longer context then has for a shorter one: the matrix
-  // kernel's splits are at least four times as long, so a longer call can need
-  // less than a shorter call on the decode kernel.
+  // The size reported is that of one-wave splits of one chunk each, as many as
+  // one launch holds: it does not fall with more keys, as the number of splits
+  // does where a split takes one chunk more (8 heads of width 128, 1 row: 1.07 MB
+  // needed at 8192 keys, 0.54 at 8200) or where the matrix kernel, whose splits
+  // are at least four chunks, takes over.  A buffer sized for a context serves
+  // every shorter one.
   AttendPlan fine;
   const int kf = R <= 8 ? (R <= 4 ? 8 : 4) * (64 / (c->head_dim * esize / 16)) : 64;
   const long cf = ((long)c->t + kf - 1) / kf + ((long)c->n_suffix + kf - 1) / kf;
-  const long pf = std::max(1L, (long)ATTEND_TARGET_BLOCKS / c->n_kv_heads), sf = (cf + pf - 1) / pf;
-  ap->total = std::max(ap->need, bytes((cf + sf - 1) / sf, &fine));
+  ap->total = std::max(ap->need, bytes(std::min(cf, std::max(1L, (long)ATTEND_TARGET_BLOCKS / c->n_kv_heads)), &fine));
   return STILL_OK;
 }
 

@@ -45,3 +45,20 @@ def test_refinement_rule_takes_the_magnitude_of_the_scale(mode):
     cfg = configs.get_workload(1).cfg
     assert (_size(cfg, 2048, 256, mode, logit_scale_cross=-1024.0) == _size(cfg, 2048, 256, mode, logit_scale_cross=1024.0)
             > _size(cfg, 2048, 256, mode, logit_scale_cross=-0.1) == _size(cfg, 2048, 256, mode, logit_scale_cross=0.1))
+
+
+@pytest.mark.parametrize("mode", [configs.MODE_BF16, configs.MODE_FP32])
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("group,nq", [(1, 1), (2, 1), (3, 1), (2, 2), (4, 2), (4, 4), (4, 8)])
+def test_attention_workspace_does_not_shrink_with_more_keys(group, nq, d, mode):
+    """Consumer attention: a buffer sized for a context serves every shorter
+    one, past the number of chunks that one launch holds and on both sides of
+    the choice between its kernels."""
+    for H in (1, 8, 40):
+        for t in (0, 655):
+            lens = sorted({*range(33, 20000, 241), *(12288 // H + x - t for x in (-1, 0, 1) if 12288 // H > t + 32),
+                           8192, 8200, 8256, 16384, 16392, 65536, 131072, 131080})
+            sizes = [binding.still_attend_workspace_size(binding.still_attend_config(H, group, d, nq, t, S, 0, 0.0, mode, 0.0))
+                     for S in lens]
+            assert sizes[0] > 0
+            assert sizes == sorted(sizes)
