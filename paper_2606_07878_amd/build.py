@@ -7,6 +7,7 @@ object."""
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 
@@ -32,6 +33,34 @@ def _filter(stderr: str) -> str:
     return "\n".join(l for l in stderr.splitlines() if "packed-fp32-ops" not in l)
 
 
+def accumulation_register_uses(asm: str) -> list:
+    """Uses of an accumulation register by the fp16 attention kernels outside
+    inline assembly, which names those that hold their accumulators outright: a
+    value of the compiler's there would overwrite them, or be overwritten."""
+    inside, kernel, found = False, "", []
+    for line in asm.splitlines():
+        m = re.match(r"^(_Z\w+):", line)
+        if m:
+            kernel = m.group(1)
+        if "#ASMSTART" in line:
+            inside = True
+        elif "#ASMEND" in line:
+            inside = False
+        elif not inside and line.startswith("\t") and not line.startswith(("\t.", "\t;")):
+            if re.search(r"accvgpr|\ba\[?\d", line.split(";")[0]) and "xattn_f16" in kernel:
+                found.append(f"{kernel}: {line.strip()}")
+    return found
+
+
+def scratch_bytes(asm: str) -> dict:
+    """Scratch bytes per lane of each fp16 attention kernel."""
+    sizes = {}
+    for m in re.finditer(r"^\s+\.name:\s+(_Z\w+)\n(?:.*\n)*?\s+\.private_segment_fixed_size:\s+(\d+)", asm, re.M):
+        if "xattn_f16" in m.group(1):
+            sizes[m.group(1)] = int(m.group(2))
+    return sizes
+
+
 def build_library(verbose: bool = False) -> str:
     """Compile the HIP library; always recompiles. Returns the library path."""
     objs = [os.path.join(CSRC, os.path.basename(src) + ".o") for src in SOURCES]
@@ -41,8 +70,11 @@ def build_library(verbose: bool = False) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True))
+    asm = os.path.join(CSRC, "xattn.s.o")
+    procs.append(subprocess.Popen([HIPCC, *FLAGS, "--cuda-device-only", "-S", "-o", asm, SOURCES[1]],
+                                  stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True))
     errors = []
-    for src, p in zip(SOURCES, procs):
+    for src, p in zip([*SOURCES, SOURCES[1]], procs):
         out, err = p.communicate()
         err = _filter(err)
         if p.returncode != 0:
@@ -51,6 +83,12 @@ def build_library(verbose: bool = False) -> str:
             print(err, file=sys.stderr)
     if errors:
         raise RuntimeError("\n".join(errors))
+    with open(asm) as f:
+        found = accumulation_register_uses(f.read())
+    os.remove(asm)
+    if found:
+        raise RuntimeError("this compiler uses accumulation registers that the fp16 attention kernels name:\n"
+                           + "\n".join(found[:5]))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     if verbose:

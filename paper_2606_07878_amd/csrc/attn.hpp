@@ -366,9 +366,14 @@ namespace still {
 // Accumulators kept in accumulation registers named outright: tile T is
 // a[16 T .. 16 T + 15].  Left to the compiler, 384 accumulator registers do not
 // fit: it moves whole tiles through scratch memory.  The kernel's own values
-// stay in the vector registers (the build has no spills and no other use of
-// accumulation registers there, tests/test_attn_registers.py), so nothing but
-// these statements touches them; being volatile they keep their order.
+// stay in the vector registers (the build fails if the compiler uses an
+// accumulation register there, build.py), so nothing but these statements
+// touches them; being volatile they keep their order.  Where the vector
+// registers do not suffice the compiler spills to scratch memory, inside the
+// loop over key blocks: about 28 registers at 128 latents x 512 keys, one or two
+// at 128 x 256 x 512 features with candidates, none elsewhere
+// (tests/test_attn_registers.py).  These transfers count as memory operations in
+// the waits below, which then wait for more than they need, never for less.
 // The compiler looks for no hazards in inline assembly: the s_nop in front
 // covers operands that a vector instruction wrote just before, acc_settle()
 // goes between the last MFMA or accumulator write and the first read of
