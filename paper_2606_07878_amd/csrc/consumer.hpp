@@ -15,15 +15,22 @@ namespace still {
 
 constexpr int ATTEND_MAX_ROWS = 32;   // group * n_queries
 // Rows per KV head up to which the register-resident decode kernel is taken
-// instead of the matrix one (bf16, us per call, decode / matrix).  8 heads, 2
-// rows: 1088 keys of width 256 11.2 / 16.0, 65600 keys 110 / 118.  4 rows over
-// few keys in all: 8 heads x 1088 keys of width 128 7.8 / 9.5 in the kernel,
-// of width 256 13.2 / 15.8; over many: 8 x 131136 of width 128 152 / 114, 64 x
-// 719 19.6 / 14.1, 8 x 65536 of width 256 160 / 114.  8 rows: 8 x 1088 keys
-// 17.5 / 11.8 and (width 256) 30.6 / 16.1.
-inline __host__ __device__ int attend_decode_rows(int d, int heads, long keys) {
+// instead of the matrix one (us per call with its merge, decode / matrix, bf16
+// unless said).  2 rows: 8 heads x 1088 keys of width 256 11.2 / 16.0, x 65600
+// 110 / 118.  4 rows over few keys in all, 8 heads of width 128: x 1024 keys
+// 10.3 / 10.6, x 1536 (the line) 11.3 / 10.9, x 4096 13.3 / 11.0, x 131136 152 /
+// 114; of width 256: x 1536 13.4 / 16.5, x 2048 14.7 / 16.7, x 3072 22.2 / 17.4;
+// 2 heads x 6144 17.9 / 17.2; of width 64 the matrix kernel throughout (x 512
+// 10.0 / 8.2).  8 rows over still fewer, rows of 512 bytes and more, 8 heads: width
+// 256 x 256 keys (the line) 14.0 / 16.1, x 384 16.8 / 16.2, x 1088 29.8 / 16.7; fp32
+// width 256 x 256 12.4 / 15.8, x 512 15.8 / 15.9; fp32 width 128 x 256 10.2 / 10.8, x
+// 384 11.4 / 10.9.
+inline __host__ __device__ int attend_decode_rows(int d, int esize, int heads, long keys) {
+  if (d * esize >= 512 && heads * keys <= 2048) return 8;
   return d >= 128 && heads * keys <= 12288 ? 4 : 2;
 }
+// 16-byte loads of a decode chunk per lane and operand, for a kernel of up to rb rows
+inline __host__ __device__ constexpr int attend_decode_nit(int rb) { return rb <= 4 ? 8 : 4; }
 constexpr int ATTEND_KC = 32;         // keys per chunk of the matrix kernel
 
 struct ConsumerArgs {
@@ -392,7 +399,7 @@ __global__ __launch_bounds__(64 * ATTEND_WAVES) void attend_rows_kernel(Consumer
 }
 
 // ---------------------------------------------------------------------------
-// Decode-shaped attention (R <= 4 query rows per KV head), no LDS in the chunk
+// Decode-shaped attention (R <= 8 query rows per KV head), no LDS in the chunk
 // loop.  A key row is PPR 16-byte pieces; LPK = PPR lanes share one key (lane
 // piece pl = lane % LPK holds features [pl*EPP, (pl+1)*EPP)), KPI = 64 / LPK
 // keys are read per instruction, NIT instructions make a chunk of KC keys.
@@ -408,7 +415,7 @@ struct DecodeTile {
   static constexpr int LPK = PPR;
   static constexpr int KPI = 64 / LPK;
   static constexpr int EPP = 16 / (int)sizeof(IT);
-  static constexpr int NIT = 8;
+  static constexpr int NIT = attend_decode_nit(RB);
   static constexpr int KC = NIT * KPI;
   static_assert(LPK >= 8 && LPK <= 64, "lanes per key");
 };

@@ -133,8 +133,8 @@ static still_status attend_plan(const still_attend_config* c, AttendPlan* ap) {
   // keys per chunk: the decode kernel's KC or ATTEND_KC
   const long R = (long)c->group * c->n_queries;
   const int esize = c->mode == STILL_MODE_FP32 ? 4 : 2;
-  const bool decode = R <= attend_decode_rows(c->head_dim, c->n_kv_heads, (long)c->t + c->n_suffix);
-  const int kc = decode ? 8 * (64 / (c->head_dim * esize / 16)) : ATTEND_KC;
+  const bool decode = R <= attend_decode_rows(c->head_dim, esize, c->n_kv_heads, (long)c->t + c->n_suffix);
+  const int kc = decode ? attend_decode_nit(R) * (64 / (c->head_dim * esize / 16)) : ATTEND_KC;
   ap->kc = kc;
   const long chunks = ((long)c->t + kc - 1) / kc + ((long)c->n_suffix + kc - 1) / kc;
   // one-wave blocks of the decode kernel; blocks of ATTEND_WAVES waves, a
@@ -159,7 +159,7 @@ static still_status attend_plan(const still_attend_config* c, AttendPlan* ap) {
   // are at least four chunks, takes over.  A buffer sized for a context serves
   // every shorter one.
   AttendPlan fine;
-  const int kf = R <= 8 ? (R <= 4 ? 8 : 4) * (64 / (c->head_dim * esize / 16)) : 64;
+  const int kf = R <= 8 ? attend_decode_nit(R) * (64 / (c->head_dim * esize / 16)) : 64;
   const long cf = ((long)c->t + kf - 1) / kf + ((long)c->n_suffix + kf - 1) / kf;
   ap->total = std::max(ap->need, bytes(std::min(cf, std::max(1L, (long)ATTEND_TARGET_BLOCKS / c->n_kv_heads)), &fine));
   return STILL_OK;
@@ -169,11 +169,13 @@ template <class IT, int D>
 static hipError_t launch_attend(const ConsumerArgs& a, hipStream_t st) {
   const int R = a.group * a.nq;
   const dim3 grid(a.splits, a.H);
-  const bool decode = R <= attend_decode_rows(D, a.H, (long)a.t + a.S);
+  const bool decode = R <= attend_decode_rows(D, sizeof(IT), a.H, (long)a.t + a.S);
   if (decode && R <= 2)
     hipLaunchKernelGGL((attend_decode_kernel<IT, D, 2>), grid, dim3(64), 0, st, a);
-  else if (decode)
+  else if (decode && R <= 4)
     hipLaunchKernelGGL((attend_decode_kernel<IT, D, 4>), grid, dim3(64), 0, st, a);
+  else if (decode)
+    hipLaunchKernelGGL((attend_decode_kernel<IT, D, 8>), grid, dim3(64), 0, st, a);
   else if (R <= 16)
     hipLaunchKernelGGL((attend_rows_kernel<IT, D, 16>), grid, dim3(64 * ATTEND_WAVES), (attend_lds_bytes<D, 16>()), st,
                        a);

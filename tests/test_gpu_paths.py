@@ -53,6 +53,9 @@ def _attend_case(H, group, nq, t, S, d, causal, mode, rotate=False):
     (2, 1, 700, 9, False),     # 2 rows: the decode kernel at every width
     (2, 2, 700, 5444, True),   # 4 rows over 2 x 6144 keys: decode kernel at widths 128 and 256
     (2, 2, 700, 5445, True),   # ... over one key more: matrix kernel
+    (4, 2, 700, 324, True),    # 8 rows over 2 x 1024 keys: decode kernel at rows of 512 bytes and more
+    (4, 2, 700, 325, True),    # ... over one key more: matrix kernel
+    (5, 1, 0, 37, False),      # 5 rows, fewer keys than one chunk of most widths
     (1, 3, 0, 65, True),       # 3 rows without a compact part
     (3, 3, 31, 33, True),      # 9 rows in the 16-row tile; chunks of 32 cut short and spilling over by one
     (4, 4, 0, 16, True),       # 16 rows: the last; fewer keys than one chunk, most of them masked for the first row
