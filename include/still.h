@@ -38,11 +38,15 @@
  *   from fp16 (bf16 mode) or fp32 operands; every key whose logit lies within
  *   10 log2 units of its latent's maximum is then recomputed accurately (fp32
  *   from split fp16 operands, or fp64) and its weight replaced.  Capacity: the
- *   256 largest such keys per latent, from at most 1536 (fp32 mode) or 8 lists
- *   of 192 (bf16 mode) candidates per latent and key split.  A bf16-mode list
- *   that fills keeps its largest entries, so that the largest key of a latent
- *   is always recomputed.  Caches with more near-maximal keys per latent (rows
- *   repeated hundreds of times) lose accuracy gradually.
+ *   256 largest such keys per latent, from at most 1536 candidates (fp32 mode)
+ *   or 8 lists of 192 candidates (bf16 mode; 128 where few latents make many
+ *   key splits) per latent and key split.  A bf16-mode list that fills keeps its
+ *   largest entries, so that the largest key of a latent is always recomputed.
+ *   Caches with more near-maximal keys per latent (rows repeated hundreds of
+ *   times) lose accuracy gradually.  Exception: where |logit scale| x log2(e)
+ *   <= 1/4 nothing is recomputed.  The QK-norm bounds the logits by the scale,
+ *   so the operands' roundings move a weight by less than half a rounding of
+ *   its own.
  * - Work is enqueued on `stream` (NULL = default stream) and the call returns
  *   without synchronising.  Arguments are validated before anything is
  *   enqueued; a non-OK status means nothing was launched.  Faults during

@@ -65,6 +65,7 @@ __global__ __launch_bounds__(256) void cross_attn_kernel(AttnArgs a) {
   typedef Mma<CT> MM;
   typedef typename MM::frag frag;
   constexpr int E = MM::E;
+  static_assert(E == 4, "fp32 operands");
   constexpr int PAD = 16 / sizeof(CT);
   constexpr int LQ = DK + PAD;           // Q/K stage row stride
   constexpr int LX = NB + PAD;           // X^T block row stride
@@ -259,36 +260,16 @@ __global__ __launch_bounds__(256) void cross_attn_kernel(AttnArgs a) {
     // ---- O^T += X^T P^T
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) {
-      if constexpr (E == 8) {
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-          half8 bp;
+      for (int qd = 0; qd < 4; ++qd) {
+        frag bp;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) bp[e] = (f16)s[kt][8 * hf + e];
-          const int key0 = kt * 32 + 16 * hf + 4 * lg;   // keys key0..+3 and key0+8..+11
+        for (int e = 0; e < 4; ++e) bp[e] = s[kt][4 * qd + e];
+        const int key0 = kt * 32 + 8 * qd + 4 * lg;     // keys key0..+3
 #pragma unroll
-          for (int f = 0; f < FT; ++f) {
-            const CT* xr = &Xs[(f * 32 + l32) * LX];
-            const half4 lo = *(const half4*)(xr + key0);
-            const half4 hi = *(const half4*)(xr + key0 + 8);
-            half8 ax;
-            ax[0] = lo[0]; ax[1] = lo[1]; ax[2] = lo[2]; ax[3] = lo[3];
-            ax[4] = hi[0]; ax[5] = hi[1]; ax[6] = hi[2]; ax[7] = hi[3];
-            MM::mma(o[f], *(const frag*)&ax, *(const frag*)&bp);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-          frag bp;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) bp[e] = s[kt][4 * qd + e];
-          const int key0 = kt * 32 + 8 * qd + 4 * lg;     // keys key0..+3
-#pragma unroll
-          for (int f = 0; f < FT; ++f) {
-            const frag ax = *(const frag*)&Xs[(f * 32 + l32) * LX + key0];
-            MM::mma(o[f], ax, bp);
-          }
+        for (int f = 0; f < FT; ++f) {
+          const frag ax = *(const frag*)&Xs[(f * 32 + l32) * LX + key0];
+          MM::mma(o[f], ax, bp);
         }
       }
     }

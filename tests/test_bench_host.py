@@ -80,3 +80,8 @@ def test_more_than_one_gpu_is_refused():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU only" in r.stderr
+
+
+def test_traffic_guard_covers_the_files_that_choose_tiles_and_splits():
+    names = {os.path.basename(f) for f in bench.KERNEL_SOURCES}
+    assert {"attn.hpp", "common.hpp", "host.hpp", "xattn.hip"} <= names
