@@ -35,7 +35,7 @@ PEAK_HBM_GBS = 8000.0
 # from rocprofv3 PMC FETCH_SIZE / WRITE_SIZE passes scaled by what the same
 # counters read for a 1 GiB device copy (factors 2.0 and 1.0).  Valid only for
 # the kernel sources with this digest; any later change reports null.
-MEASURED_TRAFFIC = {"workload": 2, "sources_sha256_16": "67018e2c494fc636", "bytes_per_launch": 3645358285}
+MEASURED_TRAFFIC = {"workload": 2, "sources_sha256_16": "6b0dc2a751f8d041", "bytes_per_launch": 3636593766}
 KERNEL_SOURCES = tuple(f"paper_2606_07878_amd/csrc/{f}" for f in ("attn.hpp", "common.hpp", "host.hpp", "xattn.hip"))
 
 

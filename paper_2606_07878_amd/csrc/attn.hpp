@@ -792,7 +792,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           const int at = 8 * (li * XATT_NBK + 2 * w + lg) * a.ccap;
           float sum = 0.f, top = -INFINITY;
 #pragma unroll 1
-          for (int i = 0; i < 32; i += NB) {
+          for (int i = 0; i < (n ? 32 : 0); i += NB) {   // (no list, no access: rows past t have no memory)
             float x[NB];
 #pragma unroll
             for (int q = 0; q < NB; ++q)

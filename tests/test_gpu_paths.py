@@ -195,3 +195,15 @@ def test_negative_logit_scale_fp32():
     at +1024."""
     w = configs.shrink(configs.get_workload(1), logit_scale_cross=-1024.0)
     _layer_case(w, configs.MODE_FP32, 1000, 130, "scale -1024")
+
+
+@pytest.mark.parametrize("t", [1, 33])
+def test_full_candidate_lists_beside_padding_rows(t):
+    """Lists that fill in lanes whose neighbours hold padding rows, which have no
+    lists: 64 splits of 2048 keys, all within the refinement margin."""
+    w = configs.shrink(configs.get_workload(1), head_dim=128, n_kv_heads=2, n_tokens=131072, t=t, n_cross_heads=8,
+                       n_self_heads=0, logit_scale_cross=0.5)
+    cache, wts = synth.make_cache(w, 0), synth.make_weights(w, 0)
+    ref = run_oracle(w.cfg, cache, wts, w.rope_theta, t, heads=[1])
+    got = run_gpu(w.cfg, cache, wts, w.rope_theta, t)
+    assert_parity((got[0][1:], got[1][1:], got[2]), ref, BF16_TOL, f"padding rows t={t}")
